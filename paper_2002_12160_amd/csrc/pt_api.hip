@@ -389,9 +389,8 @@ pt_status pt_create_batch(const pt_batch_desc *d, pt_batch *out)
     pt_status st = validate(d);
     if (st != PT_OK) return st;
     // candidate list (every sphere-link pair up to pt::CAND_CAP entries -- a
-    // step with more cuts its list to the C_max lowest and goes on -- plus 8
-    // entries of padding for the cap's 16-byte reads); the same LDS holds,
-    // once the cap has run, the rows of the solve's cross-contact sums
+    // step with more cuts its list to the C_max lowest and goes on); the same
+    // LDS holds, once the cap has run, the rows of the solve's cross-contact sums
     // (rows of RedStride<double> = 44 doubles: one per contact slot for the
     // PD solve's per-link sums, at most 32 for the kinematic solve's sums,
     // which fold the upper half-wave's contacts onto the lower one's)
@@ -406,7 +405,7 @@ pt_status pt_create_batch(const pt_batch_desc *d, pt_batch *out)
     // ... and the step's hand kinematics, which use the same LDS first
     const size_t fk_bytes = d->hand_mode == 1 ? pt::pd_fk_bytes(d->L) : hand_fk_lds_bytes(d->L, d->D);
     const int n_pairs = d->collision_mode == 1 ? d->L * d->link_samples + d->S_max : d->S_max * (d->L + 1);
-    const int list = std::min(n_pairs, pt::CAND_CAP) + 8, rows = red_rows * pt::RedStride<double>::value,
+    const int list = std::min(n_pairs, pt::CAND_CAP), rows = red_rows * pt::RedStride<double>::value,
               fk = (int)((fk_bytes + 7) / 8);
     int max_cand, max_cand_rows;
     if (d->hand_mode == 1) {

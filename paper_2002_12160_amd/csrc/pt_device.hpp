@@ -61,6 +61,18 @@ struct WaveLds {
 
 __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
+// The lane index, opaque to the compiler: masks and addresses that follow
+// from it are formed where they are used.  Used in the phases that run once a
+// step: left visible there, they were taken for invariants of the window's
+// step loop and held in registers through the Newton loop, whose peak sets
+// the occupancy.
+__device__ __forceinline__ int lane_here()
+{
+    int l = lane_id();
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
 __device__ __forceinline__ void wave_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -150,6 +162,12 @@ __device__ __forceinline__ uint64_t pack_gap_key(float d, int k)
     uint32_t u = __float_as_uint(d + 0.f);
     u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
     return ((uint64_t)u << 32) | (uint32_t)k;
+}
+
+// the gap whose packed word's upper half is u
+__device__ __forceinline__ float unpack_gap(uint32_t u)
+{
+    return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
 }
 
 // One half-wave's values in both halves: lanes i and i + 32 both end with

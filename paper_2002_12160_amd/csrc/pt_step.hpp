@@ -189,173 +189,149 @@ __device__ __forceinline__ void contact_setup(const Consts &P, const float *__re
     }
 }
 
-// The cap's ranking for ncand <= 64 H candidates (H = 1 .. 4): lane i
-// holds candidates i, i + 64, ... as packed (d, key) words (lanes past
-// ncand the largest word, never below a candidate's, so the counts run over
-// whole groups of four lanes); every word is broadcast once and each lane
-// counts the lower ones for each word it holds.  Keys are unique, so the ranks are a
-// permutation; the C_max lowest candidates' keys land in sel[rank].
-template <int H>
-__device__ __forceinline__ void cap_rank(const WaveLds &lds, int ncand, int C_max)
+// The cap's ranking for n <= 64 candidates: lane i holds candidate i as a
+// packed (d, key) word (lanes past n the largest word, never below a
+// candidate's, so the counts run over whole groups of four lanes); every
+// word is broadcast once and each lane counts the lower ones.  Keys are
+// unique, so the ranks are a permutation; the C_max lowest candidates' keys
+// land in sel[rank].
+__device__ __forceinline__ void cap_rank(const WaveLds &lds, int n, int C_max)
 {
-    const int lane = lane_id();
-    uint64_t w[H];
-    int ki[H], rank[H];
-#pragma unroll
-    for (int h = 0; h < H; ++h) {
-        const int i = lane + WAVE * h;
-        w[h] = ~0ull;
-        ki[h] = 0;
-        rank[h] = 0;
-        if (i < ncand) {
-            ki[h] = lds.cand_k[i];
-            w[h] = pack_gap_key(lds.cand_d[i], ki[h]);
-        }
+    const int lane = lane_here();
+    uint64_t w = ~0ull;
+    int ki = 0, rank = 0;
+    if (lane < n) {
+        ki = lds.cand_k[lane];
+        w = pack_gap_key(lds.cand_d[lane], ki);
     }
-#pragma unroll
-    for (int hb = 0; hb < H; ++hb) {
-        const int n = min(WAVE, ncand - WAVE * hb);
-        for (int j = 0; j < n; j += 4) {
-            const uint64_t a = bcast_lane(w[hb], j), b = bcast_lane(w[hb], j + 1);
-            const uint64_t c = bcast_lane(w[hb], j + 2), d = bcast_lane(w[hb], j + 3);
-#pragma unroll
-            for (int h = 0; h < H; ++h)
-                rank[h] += (a < w[h] ? 1 : 0) + (b < w[h] ? 1 : 0) + (c < w[h] ? 1 : 0) + (d < w[h] ? 1 : 0);
-        }
+    for (int j = 0; j < n; j += 4) {
+        const uint64_t a = bcast_lane(w, j), b = bcast_lane(w, j + 1);
+        const uint64_t c = bcast_lane(w, j + 2), d = bcast_lane(w, j + 3);
+        rank += (a < w ? 1 : 0) + (b < w ? 1 : 0) + (c < w ? 1 : 0) + (d < w ? 1 : 0);
     }
-#pragma unroll
-    for (int h = 0; h < H; ++h)
-        if (lane + WAVE * h < ncand && rank[h] < C_max) lds.sel[rank[h]] = ki[h];
+    if (lane < n && rank < C_max) lds.sel[rank] = ki;
 }
 
-// The cap for C_max < ncand <= 64 H (H = 2..4), with the same sel[] as
-// cap_rank<H>: the C_max-th lowest packed (d, key) word is found bit by bit
-// (radix select: a bit of the boundary stays set while fewer than C_max
-// words lie below the trial value, counted by ballots), first over the 32
-// gap bits and, only when several words share the boundary gap, over their
-// key bits; the C_max words up to the boundary move to the front of the
-// list and cap_rank<1> ranks them among themselves, which is their rank
-// among all candidates (every lower word is kept too).  32 rounds of H
-// compares instead of ncand broadcasts against H words per lane.
+// Cuts the list's first n entries, C_max < n <= 64 H, to their C_max lowest
+// (d, key) entries, moved to its head in list order; returns the largest
+// kept packed word.  The boundary is found bit by bit (radix select: a bit
+// of it stays set while fewer than C_max words lie below the trial value,
+// counted by ballots) over the 32 gap bits; a trial value with exactly
+// C_max words below it is the boundary already (about half of the rounds),
+// and only when several words share the boundary gap are their key bits
+// searched too.  At most 32 rounds of H compares, the words in registers,
+// instead of n broadcasts or LDS reads against H words per lane: from 256
+// to 512 candidates, where every lane used to rank its words against the
+// list in LDS, that is ~500 instead of ~5000 instructions (three control
+// steps of a fresh 16384-simulation population, ~265 candidates each: 2.25 ms
+// with the LDS ranking, 1.56 ms with the cut).
 template <int H>
-__device__ __forceinline__ void cap_select(const WaveLds &lds, int ncand, int C_max)
+__device__ __forceinline__ uint64_t cap_cut(const WaveLds &lds, int n, int C_max)
 {
-    const int lane = lane_id();
+    const int lane = lane_here();
     uint32_t hi[H], lo[H];
-    float d[H];
 #pragma unroll
     for (int h = 0; h < H; ++h) {
         const int i = lane + WAVE * h;
         hi[h] = lo[h] = ~0u;   // above every candidate: gaps are finite
-        d[h] = 0.f;
-        if (i < ncand) {
-            d[h] = lds.cand_d[i];
-            const uint64_t w = pack_gap_key(d[h], lds.cand_k[i]);
+        if (i < n) {
+            const uint64_t w = pack_gap_key(lds.cand_d[i], lds.cand_k[i]);
             hi[h] = (uint32_t)(w >> 32);
             lo[h] = (uint32_t)w;
         }
     }
-    uint32_t ph = 0;
+    uint32_t ph = 0, pl = ~0u;
+    bool exact = false;
+#pragma unroll 1
     for (int b = 31; b >= 0; --b) {
         const uint32_t t = ph | (1u << b);
         int cnt = 0;
 #pragma unroll
         for (int h = 0; h < H; ++h) cnt += __popcll(__ballot(hi[h] < t));
         if (cnt < C_max) ph = t;
+        if (cnt == C_max) {
+            ph = t - 1;
+            exact = true;
+            break;
+        }
     }
-    // ph: the boundary gap word (fewer than C_max words below it, at least
-    // C_max up to it)
-    int below = 0, at = 0;
+    // ph: the boundary gap word (exact: the C_max words up to it; otherwise
+    // fewer than C_max words below it, at least C_max up to it)
+    if (!exact) {
+        int below = 0, at = 0;
 #pragma unroll
-    for (int h = 0; h < H; ++h) {
-        below += __popcll(__ballot(hi[h] < ph));
-        at += __popcll(__ballot(hi[h] == ph));
-    }
-    uint32_t pl = ~0u;
-    if (below + at > C_max) {
-        const int need = C_max - below;
-        pl = 0;
-        for (int b = 31; b >= 0; --b) {
-            const uint32_t t = pl | (1u << b);
-            int cnt = 0;
+        for (int h = 0; h < H; ++h) {
+            below += __popcll(__ballot(hi[h] < ph));
+            at += __popcll(__ballot(hi[h] == ph));
+        }
+        if (below + at > C_max) {
+            const int need = C_max - below;
+            pl = 0;
+#pragma unroll 1
+            for (int b = 31; b >= 0; --b) {
+                const uint32_t t = pl | (1u << b);
+                int cnt = 0;
 #pragma unroll
-            for (int h = 0; h < H; ++h) cnt += __popcll(__ballot(hi[h] == ph && lo[h] < t));
-            if (cnt < need) pl = t;
+                for (int h = 0; h < H; ++h) cnt += __popcll(__ballot(hi[h] == ph && lo[h] < t));
+                if (cnt < need) pl = t;
+            }
         }
     }
     wave_sync();   // every lane has read its entries before the list is rewritten
     int base = 0;
+    uint64_t top = 0;
 #pragma unroll
     for (int h = 0; h < H; ++h) {
         const bool keep = hi[h] < ph || (hi[h] == ph && lo[h] <= pl);
         const uint64_t m = __ballot(keep);
         if (keep) {
-            const int at2 = base + mask_rank(m);
-            lds.cand_d[at2] = d[h];
-            lds.cand_k[at2] = (int)lo[h];
+            const int at = base + mask_rank(m);
+            const uint64_t w = ((uint64_t)hi[h] << 32) | lo[h];
+            lds.cand_d[at] = unpack_gap(hi[h]);
+            lds.cand_k[at] = (int)lo[h];
+            top = w > top ? w : top;
         }
         base += __popcll(m);
     }
     wave_sync();
-    cap_rank<1>(lds, C_max, C_max);
+    return top;
 }
 
-// The cap's ranking for any n: every lane ranks its candidates against the
-// LDS list, eight per pair of 16-byte reads (entries past n padded with
-// (+inf, INT_MAX), never below); the keys of the C_max lowest go to
-// sel[rank] and, with dsel, their gaps to dsel[rank].
-__device__ __forceinline__ void cap_rank_lds(const WaveLds &lds, int n, int C_max, float *dsel)
+// More than 512 entries cut piece by piece: the first 512 to their C_max
+// lowest, the dropped ones' places filled from the list's end (an entry that
+// a piece drops has C_max lower ones in it, so the result is that of one
+// cut).  Returns the new length, in (C_max, 512].
+__device__ __forceinline__ int cap_cut_pieces(const WaveLds &lds, int n, int C_max)
 {
-    const int lane = lane_id();
-    if (lane < 8) {
-        lds.cand_d[n + lane] = __int_as_float(0x7f800000);
-        lds.cand_k[n + lane] = 0x7fffffff;
-    }
-    wave_sync();
-    for (int i = lane; i < n; i += WAVE) {
-        const float di = lds.cand_d[i];
-        const int ki = lds.cand_k[i];
-        int rank = 0;
-        for (int j = 0; j < n; j += 8) {
-            const float4 d4 = *reinterpret_cast<const float4 *>(lds.cand_d + j);
-            const float4 e4 = *reinterpret_cast<const float4 *>(lds.cand_d + j + 4);
-            const int4 k4 = *reinterpret_cast<const int4 *>(lds.cand_k + j);
-            const int4 m4 = *reinterpret_cast<const int4 *>(lds.cand_k + j + 4);
-            rank += (d4.x < di || (d4.x == di && k4.x < ki)) ? 1 : 0;
-            rank += (d4.y < di || (d4.y == di && k4.y < ki)) ? 1 : 0;
-            rank += (d4.z < di || (d4.z == di && k4.z < ki)) ? 1 : 0;
-            rank += (d4.w < di || (d4.w == di && k4.w < ki)) ? 1 : 0;
-            rank += (e4.x < di || (e4.x == di && m4.x < ki)) ? 1 : 0;
-            rank += (e4.y < di || (e4.y == di && m4.y < ki)) ? 1 : 0;
-            rank += (e4.z < di || (e4.z == di && m4.z < ki)) ? 1 : 0;
-            rank += (e4.w < di || (e4.w == di && m4.w < ki)) ? 1 : 0;
+    constexpr int PIECE = 8 * WAVE;
+    while (n > PIECE) {
+        cap_cut<8>(lds, PIECE, C_max);
+        const int m = min(PIECE - C_max, n - PIECE);
+        for (int i = lane_id(); i < m; i += WAVE) {
+            lds.cand_d[C_max + i] = lds.cand_d[n - m + i];
+            lds.cand_k[C_max + i] = lds.cand_k[n - m + i];
         }
-        if (rank < C_max) {
-            lds.sel[rank] = ki;
-            if (dsel) dsel[rank] = di;
-        }
+        wave_sync();
+        n = m < PIECE - C_max ? C_max + m : n - m;
     }
+    return n;
 }
 
-// A full candidate list cut to its C_max lowest (d, key) entries, in that
-// order at its head: every candidate dropped has C_max lower ones, so the
-// cap over everything seen is unchanged.  Returns the new length; thr gets
-// the packed word of the last kept entry (the bar for later candidates).
-// The warm cache's LDS (written after the narrow phase) holds the kept gaps.
+// A full candidate list cut to its C_max lowest (d, key) entries: every
+// candidate dropped has C_max lower ones, so the cap over everything seen is
+// unchanged.  Returns the new length; thr gets the packed word of the
+// highest kept entry (the bar for later candidates).
 __device__ __forceinline__ int compact_candidates(const WaveLds &lds, int n, int C_max, uint64_t &thr)
 {
-    const int lane = lane_id();
     wave_sync();
-    cap_rank_lds(lds, n, C_max, lds.wr);
-    wave_sync();
-    const int m = min(n, C_max);
-    if (lane < m) {
-        lds.cand_d[lane] = lds.wr[lane];
-        lds.cand_k[lane] = lds.sel[lane];
+    uint64_t top = cap_cut<8>(lds, cap_cut_pieces(lds, n, C_max), C_max);
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) {
+        const uint64_t y = __shfl_xor((unsigned long long)top, o);
+        top = y > top ? y : top;
     }
-    wave_sync();
-    thr = pack_gap_key(lds.cand_d[m - 1], lds.cand_k[m - 1]);
-    return m;
+    thr = top;
+    return C_max;
 }
 
 // Narrow phase: lanes over spheres, candidates appended to LDS in (sphere
@@ -368,15 +344,17 @@ __device__ __forceinline__ int compact_candidates(const WaveLds &lds, int n, int
 // rounding) holds no candidate; the reachable links are paired in
 // increasing order, so the candidates appended, and their order, are those
 // of the full loop.
-// Bounded: the list may fill up; a batch that would overflow it first cuts
-// the list to its C_max lowest, and from then on only candidates below the
-// last kept one are appended (removed counts the others).
+// Bounded: the list may fill up; when it may not hold another pair of links
+// and the table's candidates (3 x 64 entries; with no link in reach the table
+// alone cannot fill it) it is cut to its C_max lowest, and from then on only
+// candidates below the highest kept one are appended (removed counts the
+// others).
 template <bool Bounded>
 __device__ __forceinline__ void narrow_phase(const Consts &P, const WaveLds &lds, const float (&sgr)[8],
                                              const float *__restrict__ sph, int S, const float *x, const float *R,
                                              int cap, int &ncand, int &removed)
 {
-    const int lane = lane_id();
+    const int lane = lane_here();
     const int L = P.L;
     bool bar = false;
     uint64_t thr = 0;
@@ -410,16 +388,6 @@ __device__ __forceinline__ void narrow_phase(const Consts &P, const WaveLds &lds
                     mask = __ballot(cand);
                     removed -= __popcll(mask);
                 }
-                if (ncand + __popcll(mask) > cap) {
-                    removed += ncand;
-                    ncand = compact_candidates(lds, ncand, P.C_max, thr);
-                    removed -= ncand;
-                    bar = true;
-                    cand = cand && pack_gap_key(d, k * (L + 1) + l) < thr;
-                    const uint64_t m2 = __ballot(cand);
-                    removed += __popcll(mask) - __popcll(m2);
-                    mask = m2;
-                }
             }
             if (cand) {
                 const int pos = ncand + mask_rank(mask);
@@ -430,6 +398,14 @@ __device__ __forceinline__ void narrow_phase(const Consts &P, const WaveLds &lds
         };
         // the reachable links in increasing order, two at a time
         for (uint64_t m = near; m;) {
+            if constexpr (Bounded) {
+                if (ncand + 3 * WAVE > cap) {
+                    removed += ncand;
+                    ncand = compact_candidates(lds, ncand, P.C_max, thr);
+                    removed -= ncand;
+                    bar = true;
+                }
+            }
             const int l = __builtin_ctzll(m);
             m &= m - 1;
             const int l1 = m ? __builtin_ctzll(m) : l;
@@ -456,7 +432,7 @@ __device__ __forceinline__ void narrow_phase_sdf(const Consts &P, const WaveLds 
                                                  const float *__restrict__ seg, const float *__restrict__ sph, int S,
                                                  const float *x, const float *R, int &ncand)
 {
-    const int lane = lane_id();
+    const int lane = lane_here();
     const int L = P.L, M = sdf.M, nq = L * M;
     auto append = [&](bool cand, float d, int key) {
         const uint64_t mask = __ballot(cand);
@@ -504,7 +480,7 @@ __device__ __forceinline__ void step_setup(const Consts &P, const float *__restr
                                            int wkey, const float *wr, const WaveLds &lds, StepStats &stats,
                                            StepState<SR> &st, const SdfRef &sdf = SdfRef())
 {
-    const int lane = lane_id();
+    const int lane = lane_here();
     const int L = P.L;
     step_pose<SR>(P, inv_in, B, st);
     const float *R = st.R;
@@ -520,9 +496,9 @@ __device__ __forceinline__ void step_setup(const Consts &P, const float *__restr
         sgr[0] = a.x; sgr[1] = a.y; sgr[2] = a.z; sgr[3] = a.w;
         sgr[4] = b.x; sgr[5] = b.y; sgr[6] = b.z; sgr[7] = b.w;
     }
-    // list capacity (entries; 8 more are the cap's padding); a step that
-    // can find more candidates than that runs the bounded form
-    const int cap = P.max_cand - 8;
+    // list capacity (entries); a step that can find more candidates than
+    // that runs the bounded form
+    const int cap = P.max_cand;
     int ncand = 0, removed = 0;
     if (SDF)
         narrow_phase_sdf(P, lds, sdf, seg, sph, S, B.x, R, ncand);
@@ -538,24 +514,18 @@ __device__ __forceinline__ void step_setup(const Consts &P, const float *__restr
     st.span = lane_span(C);
 
     // 3. cap: rank of every candidate in (d, key) order; the C_max lowest
-    //    land in sel[rank].  Up to one wave of candidates each lane holds
-    //    one as a packed (d, key) word and counts the lower words,
-    //    broadcast lane by lane; up to four, a radix select finds the
-    //    C_max lowest first and only they are ranked; beyond, every lane
-    //    ranks its candidates against the LDS list, eight per pair of
-    //    16-byte reads (entries past ncand padded with (+inf, INT_MAX),
-    //    never below).
-    if (ncand <= WAVE) {
-        cap_rank<1>(lds, ncand, P.C_max);
-    } else if (ncand <= 2 * WAVE) {
-        cap_select<2>(lds, ncand, P.C_max);
-    } else if (ncand <= 3 * WAVE) {
-        cap_select<3>(lds, ncand, P.C_max);
-    } else if (ncand <= 4 * WAVE) {
-        cap_select<4>(lds, ncand, P.C_max);
-    } else {
-        cap_rank_lds(lds, ncand, P.C_max, nullptr);
+    //    land in sel[rank].  More than one wave of candidates are first cut
+    //    to the C_max lowest by a radix select over as many words per lane
+    //    as there are (its registers and compares grow with them); then
+    //    each lane holds one as a packed (d, key) word and counts the lower
+    //    words, broadcast lane by lane.
+    if (ncand > WAVE) {
+        const int n = cap_cut_pieces(lds, ncand, P.C_max);
+        if (n <= 2 * WAVE) cap_cut<2>(lds, n, P.C_max);
+        else if (n <= 4 * WAVE) cap_cut<4>(lds, n, P.C_max);
+        else cap_cut<8>(lds, n, P.C_max);
     }
+    cap_rank(lds, ncand > WAVE ? P.C_max : ncand, P.C_max);
     // previous warm cache to LDS for the key lookup
     lds.wkey[lane] = wkey;
     lds.wr[3 * lane + 0] = wr[0];
