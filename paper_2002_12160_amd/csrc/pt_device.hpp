@@ -87,10 +87,11 @@ __device__ __forceinline__ int mask_rank(uint64_t mask)
 
 // Cross-lane sums with DPP (data-parallel primitives: VALU lane moves, no LDS
 // round trip).  Prefix sums inside each 16-lane row (row_shr 1, 2, 4, 8),
-// then row 0's total is added into row 1 and row 2's into row 3
-// (row_bcast:15), then lane 31 into rows 2-3 (row_bcast:31); the total ends in
-// the last lane of the span and is broadcast with readlane, so every lane gets
-// the same bits.  `span` (16, 32 or 64, wave-uniform) is the number of lanes
+// then each row's total is added into the next row (row_bcast:15), then
+// lane 31 into rows 2-3 (row_bcast:31); the total ends in the last lane of the
+// span and is broadcast with readlane, so every lane gets the same bits.  (The
+// broadcasts also reach rows whose sums nobody reads: masking those rows out
+// takes two more instructions a word, to clear the unwritten lanes.)  `span` (16, 32 or 64, wave-uniform) is the number of lanes
 // that can hold non-zero values.
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ float dpp_f(float v)
@@ -204,7 +205,7 @@ __device__ __forceinline__ void half_sums(T v, int span, T &lo, T &hi)
         hi = bcast_lane(v, 47);
         return;
     }
-    v += dpp_f<0x142, 0xa>(v);  // row_bcast:15 into rows 1, 3
+    v += dpp_f<0x142, 0xf>(v);  // row_bcast:15
     lo = bcast_lane(v, 31);
     hi = bcast_lane(v, 63);
 }
@@ -226,14 +227,14 @@ __device__ __forceinline__ void wave_sum(T (&v)[N], int span = 64)
         return;
     }
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] += dpp_f<0x142, 0xa>(v[i]);  // row_bcast:15 into rows 1, 3
+    for (int i = 0; i < N; ++i) v[i] += dpp_f<0x142, 0xf>(v[i]);  // row_bcast:15
     if (span <= 32) {
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] = bcast_lane(v[i], 31);
         return;
     }
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] += dpp_f<0x143, 0xc>(v[i]);  // row_bcast:31 into rows 2, 3
+    for (int i = 0; i < N; ++i) v[i] += dpp_f<0x143, 0xf>(v[i]);  // row_bcast:31
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = bcast_lane(v[i], 63);
 }
@@ -726,7 +727,7 @@ __device__ __forceinline__ float fold_halves(float a, float b)
 // n16 rows of RedStride<T> elements.  The sums stay valid until the next
 // write to buf.
 template <typename T, int N>
-__device__ __forceinline__ void lds_colsum(const T (&v)[N], int n, T *buf)
+__device__ __forceinline__ void lds_colsum(const T (&v)[N], int n, T *buf, T plus = T(0))
 {
     constexpr int RS = RedStride<T>::value;
     constexpr int PER = 16 / (int)sizeof(T);
@@ -777,7 +778,7 @@ __device__ __forceinline__ void lds_colsum(const T (&v)[N], int n, T *buf)
     }
     const T s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
     wave_sync();
-    if (lane < N) buf[lane] = s;
+    if (lane < N) buf[lane] = s + plus;
     wave_sync();
 }
 
@@ -864,21 +865,42 @@ __device__ __forceinline__ void body_mass(float m, const float *Iinv, const floa
     for (int i = 0; i < 9; ++i) M.blk[i] = uniform(M.blk[i]);
 }
 
+// Lane j's entry of M in the inertia form, at its place j in the sums
+// (row-major 6x6, then the right-hand side): the term schur_solve<SR, true>
+// expects to find added.  One add in one lane instead of twelve in every one.
+template <typename SR>
+__device__ __forceinline__ SR body_mass_entry(const BodyMass<SR> &M)
+{
+    const int lane = lane_id();
+    SR v = SR(0);
+    if (M.inertia_form) {
+        if (lane == 0 || lane == 7 || lane == 14) v = M.sc;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (lane == 6 * (3 + i) + 3 + j) v = M.blk[3 * i + j];
+    }
+    return v;
+}
+
 // Solves (I + M^-1 A6) z = -M^-1 b6 for the summed acc (A6 = acc[0..35],
 // b6 = acc[36..41]); with finite inertias as (M + A6) z = -b6, the same z
-// without forming M^-1 A6.  Result in z.
-template <typename SR>
+// without forming M^-1 A6 (Added: acc holds M + A6 then).  Result in z.
+template <typename SR, bool Added = false>
 __device__ __forceinline__ void schur_solve(const SR *acc, const BodyMass<SR> &M, SR (&z)[6])
 {
     SR S6[36];
     if (M.inertia_form) {
 #pragma unroll
         for (int i = 0; i < 36; ++i) S6[i] = acc[i];
-        S6[0] += M.sc; S6[7] += M.sc; S6[14] += M.sc;
+        if (!Added) {
+            S6[0] += M.sc; S6[7] += M.sc; S6[14] += M.sc;
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+            for (int i = 0; i < 3; ++i)
 #pragma unroll
-            for (int j = 0; j < 3; ++j) S6[6 * (3 + i) + 3 + j] += M.blk[3 * i + j];
+                for (int j = 0; j < 3; ++j) S6[6 * (3 + i) + 3 + j] += M.blk[3 * i + j];
+        }
 #pragma unroll
         for (int i = 0; i < 6; ++i) z[i] = -acc[36 + i];
     } else {

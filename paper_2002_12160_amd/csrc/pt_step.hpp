@@ -125,7 +125,10 @@ __device__ __forceinline__ void contact_setup(const Consts &P, const float *__re
     st.act = key >= 0;
     st.key = key;
     SR *F = st.F;
-    F[0] = 0; F[1] = 0; F[2] = 1; F[3] = 0; F[4] = 1; F[5] = 0; F[6] = 1; F[7] = 0; F[8] = 0;
+    // an empty slot's frame is zero, and with it everything it would add to
+    // the solve's sums
+#pragma unroll
+    for (int i = 0; i < 9; ++i) F[i] = SR(0);
     st.rho[0] = st.rho[1] = st.rho[2] = SR(0);
     st.ucst[0] = st.ucst[1] = st.ucst[2] = SR(0);
     st.r[0] = st.r[1] = st.r[2] = SR(0);
@@ -597,6 +600,13 @@ __device__ __forceinline__ void step_solve(const Consts &P, StepState<SR> &st, f
         rel_velocity(st, nu, r, eps, u);
         FBOut<SR> fo;
         fb_value(mu, kap, del, r, u, fo);
+        const SR mass = body_mass_entry(Mb);
+        // the merit at the current impulses: in float64 that of the line
+        // search's accepted trial (one sum fewer per iteration)
+        SR psi = SR(0);
+        if (sizeof(SR) == 8)
+            psi = wave_sum1(act ? SR(0.5) * (fo.phi[0] * fo.phi[0] + fo.phi[1] * fo.phi[1] + fo.phi[2] * fo.phi[2])
+                                : SR(0), span);
         for (int it = 0; it < P.newton_iters; ++it) {
             SR JX[9], JY[9];
             fb_jacobian(mu, kap, u, fo, JX, JY);
@@ -618,7 +628,10 @@ __device__ __forceinline__ void step_solve(const Consts &P, StepState<SR> &st, f
 #pragma unroll
                 for (int j = 0; j < 3; ++j)
                     QF[3 * i + j] = Q[3 * i] * F[j] + Q[3 * i + 1] * F[3 + j] + Q[3 * i + 2] * F[6 + j];
-            SR acc[43];
+            // the merit is summed with the system only in float32, where the
+            // line search's tree would round it differently
+            constexpr int NS = sizeof(SR) == 8 ? 42 : 43;
+            SR acc[NS];
             SR Qw[9];
 #pragma unroll
             for (int i = 0; i < 3; ++i)
@@ -628,18 +641,16 @@ __device__ __forceinline__ void step_solve(const Consts &P, StepState<SR> &st, f
             SR gw[3] = {F[0] * g[0] + F[3] * g[1] + F[6] * g[2], F[1] * g[0] + F[4] * g[1] + F[7] * g[2],
                         F[2] * g[0] + F[5] * g[1] + F[8] * g[2]};
             schur_contribution(Qw, gw, rho, acc);
-            acc[42] = SR(0.5) * (fo.phi[0] * fo.phi[0] + fo.phi[1] * fo.phi[1] + fo.phi[2] * fo.phi[2]);
-            if (!act) {
-#pragma unroll
-                for (int i = 0; i < 43; ++i) acc[i] = SR(0);
-            }
+            if constexpr (NS == 43)
+                acc[42] = act ? SR(0.5) * (fo.phi[0] * fo.phi[0] + fo.phi[1] * fo.phi[1] + fo.phi[2] * fo.phi[2])
+                              : SR(0);
             // the sums stay valid in LDS until the next iteration's rows; the
             // 6x6 solve reads them from there as it goes (fewer live
-            // registers than loading all 43 at once)
+            // registers than loading them all at once)
             SR rhs[6];
-            lds_colsum<SR, 43>(acc, st.C, red);
-            const SR psi = red[42];
-            schur_solve(red, Mb, rhs);
+            lds_colsum<SR, NS>(acc, st.C, red, mass);
+            if constexpr (NS == 43) psi = red[42];
+            schur_solve<SR, true>(red, Mb, rhs);
             // dr = -g - Q F (dv + dw x rho)
             SR dp[3];
             SR dw3[3] = {rhs[3], rhs[4], rhs[5]};
@@ -757,6 +768,7 @@ __device__ __forceinline__ void step_solve(const Consts &P, StepState<SR> &st, f
                 u[i] = ut[i];
             }
             fo = ft;
+            if (sizeof(SR) == 8) psi = st.psi_end;
 #pragma unroll
             for (int i = 0; i < 6; ++i) nu[i] += alpha * dn[i];
         }
