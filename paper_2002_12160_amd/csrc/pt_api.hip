@@ -112,6 +112,12 @@ struct pt_batch_s {
     float *d_seg = nullptr;      // [L][16] the last step's hand segments (kinematic hand)
     int n_elite = 0;
     int32_t *d_elite = nullptr;  // [n_elite]
+    int32_t *d_elite_start = nullptr;            // [G] elites of the lower groups
+    int32_t *d_rank = nullptr, *d_by_rank = nullptr; // [K] the resampler's ranks and order
+    int2 *d_pieces = nullptr;    // the groups in pieces for ranking, then for the copies
+    int n_rank_pieces = 0, n_copy_pieces = 0;
+    pt::Pieces rank_pieces() const { return {d_pieces, n_rank_pieces}; }
+    pt::Pieces copy_pieces() const { return {d_pieces + n_rank_pieces, n_copy_pieces}; }
     float *d_ref = nullptr;      // see refine_layout
     float *d_snap = nullptr;     // [18][K] + [K][C_max][4]: parents' copies for the weighted resamplers
     void *static_scratch = nullptr; // this device's pt_run_window_static scratch (not owned)
@@ -451,9 +457,9 @@ pt_status pt_create_batch(const pt_batch_desc *d, pt_batch *out)
     b->warm = d->warm;
     b->group_start.assign(d->group_start, d->group_start + d->G + 1);
     for (int g = 0; g < d->G; ++g) b->max_group = std::max(b->max_group, b->group_start[g + 1] - b->group_start[g]);
-    if (pt::resample_lds_bytes(b->max_group) > 160 * 1024) {
+    if (b->max_group > pt::MAX_GROUP) {
         delete b;
-        return fail(PT_E_UNSUPPORTED, "group of %d simulations exceeds the resampler's LDS (max 16384)", b->max_group);
+        return fail(PT_E_UNSUPPORTED, "group of %d simulations exceeds the resampler's LDS (max %d)", b->max_group, pt::MAX_GROUP);
     }
 
     auto cleanup = [&](pt_status code) {
@@ -499,8 +505,24 @@ pt_status pt_create_batch(const pt_batch_desc *d, pt_batch *out)
     HIP_TRY_C(hipMalloc(&b->d_contacts, sizeof(float) * K * d->C_max * 4));
     HIP_TRY_C(hipMalloc(&b->d_seg_grad, sizeof(float) * (size_t)d->T * d->L * pt::SEG_STRIDE));
     HIP_TRY_C(hipMalloc(&b->d_tune, sizeof(float) * tune_floats(P)));
-    for (int g = 0; g < d->G; ++g)
+    std::vector<int32_t> elite_start(d->G);
+    std::vector<int2> pieces;
+    for (int chunk : {pt::RANK_CHUNK, pt::COPY_CHUNK}) {
+        for (int g = 0; g < d->G; ++g)
+            for (int i = 0; i < d->group_start[g + 1] - d->group_start[g]; i += chunk) pieces.push_back(make_int2(g, i));
+        if (chunk == pt::RANK_CHUNK) b->n_rank_pieces = (int)pieces.size();
+    }
+    b->n_copy_pieces = (int)pieces.size() - b->n_rank_pieces;
+    for (int g = 0; g < d->G; ++g) {
+        elite_start[g] = b->n_elite;
         b->n_elite += pt::elite_count(d->group_start[g + 1] - d->group_start[g], d->elite_frac);
+    }
+    HIP_TRY_C(hipMalloc(&b->d_elite_start, sizeof(int32_t) * d->G));
+    HIP_TRY_C(hipMalloc(&b->d_pieces, sizeof(int2) * pieces.size()));
+    HIP_TRY_C(hipMalloc(&b->d_rank, sizeof(int32_t) * K));
+    HIP_TRY_C(hipMalloc(&b->d_by_rank, sizeof(int32_t) * K));
+    HIP_TRY_C(hipMemcpy(b->d_elite_start, elite_start.data(), sizeof(int32_t) * d->G, hipMemcpyHostToDevice));
+    HIP_TRY_C(hipMemcpy(b->d_pieces, pieces.data(), sizeof(int2) * pieces.size(), hipMemcpyHostToDevice));
     HIP_TRY_C(hipMalloc(&b->d_ckpt, sizeof(float) * ckpt_floats(P, b->n_elite)));
     HIP_TRY_C(hipMalloc(&b->d_ref, sizeof(float) * refine_floats(P, b->n_elite)));
     HIP_TRY_C(hipMalloc(&b->d_elite, sizeof(int32_t) * b->n_elite));
@@ -573,7 +595,7 @@ pt_status pt_destroy_batch(pt_batch b)
     void *ptrs[] = {b->d_hand, b->d_spheres, b->d_inv, b->d_nsph, b->d_type, b->d_group_of, b->d_group_start,
                     b->d_order, b->d_queue, b->d_stats, b->d_seg_win, b->d_contacts,
                     b->d_seg_grad, b->d_tune, b->d_ckpt, b->d_wckpt, b->d_elite, b->d_ref, b->d_snap,
-                    b->d_cslip, b->d_seg, b->d_pd, b->d_parent, b->d_pd_obs, b->d_sdf, b->d_sdf_box};
+                    b->d_elite_start, b->d_rank, b->d_by_rank, b->d_pieces, b->d_cslip, b->d_seg, b->d_pd, b->d_parent, b->d_pd_obs, b->d_sdf, b->d_sdf_box};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     delete b;
@@ -650,8 +672,8 @@ pt_status pt_resample(pt_batch b, float *cost_sum, uint32_t window_idx, int32_t 
     if (!cost_sum) return fail(PT_E_ARG, "cost_sum is NULL");
     // the PD hand's joint state follows each simulation's parent
     int32_t *par = b->hand_mode == 1 && !parent ? b->d_parent : parent;
-    HIP_TRY(launch_resample(b->P, b->R, b->d_group_start, b->max_group, window_idx, cost_sum, b->state, b->params,
-                            b->warm, par, (hipStream_t)s));
+    HIP_TRY(launch_resample(b->P, b->R, b->d_group_start, b->max_group, b->rank_pieces(), b->copy_pieces(), window_idx,
+                            cost_sum, b->d_rank, b->d_by_rank, b->state, b->params, b->warm, par, (hipStream_t)s));
     if (b->hand_mode == 1 && b->P.D > 0)
         HIP_TRY(launch_copy_hand(b->P.K, 2 * b->P.D, par, b->hstate, (hipStream_t)s));
     return PT_OK;
@@ -934,9 +956,8 @@ pt_status pt_refine_elites(pt_batch b, const float *u_win, const float *obs_gt_w
     const int n = b->n_elite;
     RefineBufs r = refine_layout(b->d_ref, P, n);
     const Tables tb = tables_of(b);
-    HIP_TRY(launch_select_elites(P.G, b->max_group, b->R.elite_frac, b->d_group_start, cost_sum, b->d_elite, st));
-    if (elite_out)
-        HIP_TRY(hipMemcpyAsync(elite_out, b->d_elite, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st));
+    HIP_TRY(launch_rank(b->rank_pieces(), b->max_group, b->R.elite_frac, b->d_group_start, b->d_elite_start, cost_sum,
+                        nullptr, nullptr, b->d_elite, elite_out, st));
     if (steps > 0) {
         HIP_TRY(launch_hand_fk(b->d_hand, P.L, P.D, P.dt, u_win, u_win + P.D, P.D, P.T, b->d_seg_grad, st));
         // the first gradient: from the checkpoints the population's window

@@ -13,8 +13,7 @@
 //                     (implicit differentiation of the contact solve).
 //                     Output: the gradient of the window cost with respect
 //                     to the start (x, q, v, w, m, mu, f)
-//   k_select_elites   per group, the simulations of lowest window cost (the
-//                     same ranking the resampler keeps)
+//   (the elites come from the resampler's own ranking, k_rank)
 //   k_refine_*        gather / scaled gradient step / accept-or-halve
 #include "pt_adjoint.hpp"
 #include "pt_internal.h"
@@ -188,26 +187,6 @@ __global__ __launch_bounds__(WAVE) void k_window_bwd(Consts P, Tables tb, const 
     }
 }
 
-// one workgroup per group: its elites (lowest (cost, index), NaN ranked as
-// +inf; count max(1, floor(n elite_frac))) go to elite_env[offset + rank],
-// offset = number of elites of the lower groups
-__global__ __launch_bounds__(1024) void k_select_elites(int G, float elite_frac, const int32_t *__restrict__ group_start,
-                                                        const float *__restrict__ cost_sum, int32_t *__restrict__ elite_env)
-{
-    extern __shared__ __align__(16) char smem[];
-    const int g = blockIdx.x;
-    if (g >= G) return;
-    int off = 0;
-    for (int h = 0; h < g; ++h) off += elite_count(group_start[h + 1] - group_start[h], elite_frac);
-    const int lo = group_start[g], n = group_start[g + 1] - lo;
-    const int np2 = sort_slots(n);
-    const int kb = elite_count(n, elite_frac);
-    float *cs = reinterpret_cast<float *>(smem);
-    int *order = reinterpret_cast<int *>(smem + 4 * (size_t)np2);
-    sort_group(cost_sum + lo, n, np2, cs, order);
-    for (int t = threadIdx.x; t < kb; t += blockDim.x) elite_env[off + t] = lo + order[t];
-}
-
 // start of each listed simulation from the window-start snapshot (and, if
 // cost_sum is given, its window cost)
 __global__ void k_refine_gather(int n, int K, int C_max, const int32_t *__restrict__ env,
@@ -337,15 +316,6 @@ hipError_t launch_window_bwd(const Consts &P, const Tables &tb, const float *seg
     return hipGetLastError();
 }
 
-hipError_t launch_select_elites(int G, int max_group, float elite_frac, const int32_t *group_start,
-                                const float *cost_sum, int32_t *elite_env, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_select_elites, dim3(G), dim3(group_threads(max_group)), resample_lds_bytes(max_group), s,
-                       G, elite_frac,
-                       group_start, cost_sum, elite_env);
-    return hipGetLastError();
-}
-
 hipError_t launch_refine_gather(int n, int K, int C_max, const int32_t *env, const float *state, const float *params,
                                 const float *warm, const float *cost_sum, float *xi, float *warm0, float *cost,
                                 float *rho, float rho0, hipStream_t s)
@@ -378,8 +348,7 @@ hipError_t launch_refine_accept(int n, int i0, int count, int K, int C_max, cons
 
 hipError_t set_grad_lds_limits(size_t bytes)
 {
-    const void *fs[] = {reinterpret_cast<const void *>(k_select_elites),
-                        reinterpret_cast<const void *>(k_window_fwd<float, false>),
+    const void *fs[] = {reinterpret_cast<const void *>(k_window_fwd<float, false>),
                         reinterpret_cast<const void *>(k_window_fwd<double, false>),
                         reinterpret_cast<const void *>(k_window_fwd<float, true>),
                         reinterpret_cast<const void *>(k_window_fwd<double, true>),

@@ -52,26 +52,22 @@ __host__ __device__ inline int elite_count(int n, float elite_frac)
     return kb < 1 ? 1 : (kb > n ? n : kb);
 }
 
-// slots of one group's sort: the next power of two
-__host__ __device__ constexpr int sort_slots(int n)
-{
-    int p = 1;
-    while (p < n) p <<= 1;
-    return p;
-}
+// simulations per group, at most (a group's costs and the weighted draw's
+// running sums fit in one workgroup's LDS)
+constexpr int MAX_GROUP = 16384;
 
-// threads of a per-group workgroup (sort, resample, elites): one per
-// simulation of the largest group, in whole wavefronts, 64 to 1024
-constexpr int group_threads(int max_group)
-{
-    return max_group >= 1024 ? 1024 : (max_group <= 64 ? 64 : (max_group + 63) / 64 * 64);
-}
+// The resampler ranks and copies a group of up to RESAMPLE_ONE simulations in
+// one workgroup; larger groups are ranked RANK_CHUNK simulations per
+// workgroup and copied COPY_CHUNK per workgroup, over the whole GPU
+constexpr int RESAMPLE_ONE = 256;
+constexpr int RANK_CHUNK = WAVE;
+constexpr int COPY_CHUNK = 16;
 
-// LDS of one group's sort: costs and indices over sort_slots(max_group)
-__host__ __device__ constexpr size_t resample_lds_bytes(int max_group)
-{
-    return (size_t)8 * (size_t)sort_slots(max_group);
-}
+// a population's groups cut into pieces: (group, first simulation within it)
+struct Pieces {
+    const int2 *piece;
+    int count;
+};
 
 // bytes of LDS per wavefront: candidate (d, key) list, selected keys,
 // previous warm keys and impulses, contact staging for the observation, the
@@ -112,8 +108,15 @@ hipError_t launch_observe(const pt::Consts &P, const float *contacts, const floa
 hipError_t launch_cost(const pt::Consts &P, const int32_t *group_of, const int32_t *group_start, const float *obs,
                        const float *obs_gt, float *cost_sum, int32_t *best, int32_t *done, hipStream_t s);
 hipError_t launch_argmin(int G, const int32_t *group_start, const float *cost, int32_t *best, hipStream_t s);
+// the groups' simulations ranked by (cost, index), NaN as +inf: rank [K] (the
+// rank within its group), order [K] (by group, then rank: batch indices);
+// elites (by group, then rank) to elite0 and elite1; any of the four may be NULL
+hipError_t launch_rank(const pt::Pieces &rank_pieces, int max_group, float elite_frac, const int32_t *group_start,
+                       const int32_t *elite_start, const float *cost_sum, int32_t *rank, int32_t *order,
+                       int32_t *elite0, int32_t *elite1, hipStream_t s);
 hipError_t launch_resample(const pt::Consts &P, const pt::ResampleArgs &R, const int32_t *group_start, int max_group,
-                           uint32_t window_idx, float *cost_sum, float *state, float *params, float *warm,
+                           const pt::Pieces &rank_pieces, const pt::Pieces &copy_pieces, uint32_t window_idx,
+                           float *cost_sum, int32_t *rank, int32_t *order, float *state, float *params, float *warm,
                            int32_t *parent, hipStream_t s);
 hipError_t launch_window(const pt::Consts &P, const pt::Tables &tb, const float *seg_win, float *state, float *params,
                          float *warm, const float *obs_gt_win, float *cost_sum, float *obs_out,
@@ -131,8 +134,6 @@ hipError_t launch_window_bwd(const pt::Consts &P, const pt::Tables &tb, const fl
                              int count, const int32_t *env, const float *xi, const float *obs_gt_win,
                              const float *ckpt, bool ckpt_by_env, const int32_t *flag, float *grad,
                              hipStream_t s);
-hipError_t launch_select_elites(int G, int max_group, float elite_frac, const int32_t *group_start,
-                                const float *cost_sum, int32_t *elite_env, hipStream_t s);
 hipError_t launch_refine_gather(int n, int K, int C_max, const int32_t *env, const float *state, const float *params,
                                 const float *warm, const float *cost_sum, float *xi, float *warm0, float *cost,
                                 float *rho, float rho0, hipStream_t s);

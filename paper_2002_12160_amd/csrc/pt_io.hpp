@@ -337,42 +337,38 @@ __device__ __forceinline__ int load_contact(const float *__restrict__ ck, int C_
     return (int)b.y;
 }
 
-// One group's simulations in (cost, index) order, NaN ranked as +inf: a
-// bitonic sort in LDS over np2 slots (a power of two >= n, padding (+inf,
-// index >= n) sorts after every real entry).  All threads of the block take
-// part; afterwards ix[0..n) holds the group's local indices in order.
-__device__ __forceinline__ void sort_group(const float *__restrict__ cost, int n, int np2, float *cs, int *ix)
+// Number of the group's entries j in [j0, j1) that come before entry i in
+// (cost, index) order: cs holds the group's costs (NaN as +inf, padded with
+// +inf to a multiple of four), ci = cs[i]; i lies in [i0, i1).  j0, j1, i0 and
+// i1 are multiples of four and the same for the whole wavefront, so every
+// cost is one broadcast LDS read and, outside the block of i, one compare
+// (equal costs count below the block and not above it).
+__device__ __forceinline__ int rank_count(const float *cs, int j0, int j1, int i, int i0, int i1, float ci)
 {
-    for (int i = threadIdx.x; i < np2; i += blockDim.x) {
-        const float v = i < n ? cost[i] : __int_as_float(0x7f800000);
-        cs[i] = (v != v) ? __int_as_float(0x7f800000) : v;
-        ix[i] = i;
+    int r = 0;
+    for (int j = j0; j < min(j1, i0); j += 4) {
+        const float4 c = *reinterpret_cast<const float4 *>(cs + j);
+        r += (c.x <= ci ? 1 : 0) + (c.y <= ci ? 1 : 0) + (c.z <= ci ? 1 : 0) + (c.w <= ci ? 1 : 0);
     }
-    __syncthreads();
-    for (int k = 2; k <= np2; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < np2; i += blockDim.x) {
-                const int p = i ^ j;
-                if (p > i) {
-                    const float ci = cs[i], cp = cs[p];
-                    const int xi = ix[i], xp = ix[p];
-                    // entries are distinct (indices are), so "after" is strict
-                    const bool after = ci > cp || (ci == cp && xi > xp);
-                    if (after == ((i & k) == 0)) {
-                        cs[i] = cp; cs[p] = ci;
-                        ix[i] = xp; ix[p] = xi;
-                    }
-                }
-            }
-            // a stage with j < WAVE stays inside each wavefront's 64-index
-            // blocks (blockDim is a multiple of WAVE, so one wavefront owns
-            // a block), where the wavefront's own LDS order suffices; a
-            // workgroup barrier only around the stages that cross them
-            const int jn = j > 1 ? j >> 1 : k;   // the next stage's j
-            if (j >= WAVE || (jn >= WAVE && k < np2)) __syncthreads();
-            else wave_sync();
-        }
-    __syncthreads();
+    auto before = [&](float c, int j) { return c < ci || (c == ci && j < i) ? 1 : 0; };
+    for (int j = max(j0, i0); j < min(j1, i1); j += 4) {
+        const float4 c = *reinterpret_cast<const float4 *>(cs + j);
+        r += before(c.x, j) + before(c.y, j + 1) + before(c.z, j + 2) + before(c.w, j + 3);
+    }
+    for (int j = max(j0, i1); j < j1; j += 4) {
+        const float4 c = *reinterpret_cast<const float4 *>(cs + j);
+        r += (c.x < ci ? 1 : 0) + (c.y < ci ? 1 : 0) + (c.z < ci ? 1 : 0) + (c.w < ci ? 1 : 0);
+    }
+    return r;
+}
+
+// a group's n costs into LDS for rank_count, all threads of the block
+__device__ __forceinline__ void stage_costs(const float *__restrict__ cost, int n, float *cs)
+{
+    for (int i = threadIdx.x; i < ((n + 3) & ~3); i += blockDim.x) {
+        const float v = i < n ? cost[i] : __int_as_float(0x7f800000);
+        cs[i] = v != v ? __int_as_float(0x7f800000) : v;
+    }
 }
 
 // True in every thread of the workgroup that arrives last among the grid's

@@ -8,9 +8,12 @@
 //   k_observe      per-sensor contact force of the last step
 //   k_cost         step cost against the observed force, running sum (Eq. 1)
 //   k_argmin       per-group argmin of the running cost (Eq. 2)
+//   k_rank         the groups' simulations ranked by running cost
 //   k_resample     population-based resampling with Philox4x32-10 (Sec. III-D.3)
 //   k_window       batched path: persistent kernel running T steps with the
 //                  observation and cost fused, state kept on chip
+#include <algorithm>
+
 #include "pt_internal.h"
 #include "pt_io.hpp"
 
@@ -421,103 +424,139 @@ __global__ void k_argmin(const int32_t *__restrict__ group_start, const float *_
 // ---------------------------------------------------------------------
 // population-based resampling
 // ---------------------------------------------------------------------
-// copy item i of a resample (i < nr: simulation kb + i / rows of the sorted
-// group, row or slot i % rows) read from its parent / written to the child
-__device__ __forceinline__ float state_row_src(const float *state, int K, int kb, const int *par, int nr, int i)
+// Ranks by counting: a workgroup takes 64 simulations of a group, one per
+// lane, and its wavefronts each count the lower entries in their share of
+// the group's costs.  n^2 / 64 broadcast reads and n^2 compares a group, but
+// over the whole GPU and with one barrier, where a bitonic sort in one
+// workgroup per group has log^2 n dependent stages.  Bound by latency: 8 us
+// for 16 groups of 1024 (the sort: 22).
+__global__ __launch_bounds__(1024) void k_rank(float elite_frac, const int2 *__restrict__ piece,
+                                               const int32_t *__restrict__ group_start,
+                                               const int32_t *__restrict__ elite_start,
+                                               const float *__restrict__ cost_sum, int32_t *__restrict__ rank,
+                                               int32_t *__restrict__ order, int32_t *__restrict__ elite0,
+                                               int32_t *__restrict__ elite1)
 {
-    if (i >= nr * 13) return 0.f;
-    const int t = kb + i / 13, c = i - (i / 13) * 13;
-    return state[(size_t)c * K + par[t]];
-}
-__device__ __forceinline__ void state_row_dst(float *state, int K, int lo, int kb, const int *order, int nr, int i,
-                                              float v)
-{
-    if (i >= nr * 13) return;
-    const int t = kb + i / 13, c = i - (i / 13) * 13;
-    state[(size_t)c * K + lo + order[t]] = v;
-}
-__device__ __forceinline__ float4 warm_slot_src(const float4 *w4, int C, int kb, const int *par, int nr, int i)
-{
-    if (i >= nr * C) return make_float4(0.f, 0.f, 0.f, 0.f);
-    const int t = kb + i / C, c = i - (i / C) * C;
-    return w4[(size_t)par[t] * C + c];
-}
-__device__ __forceinline__ void warm_slot_dst(float4 *w4, int C, int lo, int kb, const int *order, int nr, int i,
-                                              float4 v)
-{
-    if (i >= nr * C) return;
-    const int t = kb + i / C, c = i - (i / C) * C;
-    w4[(size_t)(lo + order[t]) * C + c] = v;
+    extern __shared__ __align__(16) float cs[];
+    __shared__ int part[1024 / WAVE][WAVE];
+    const int2 pc = piece[blockIdx.x];
+    const int lo = group_start[pc.x], n = group_start[pc.x + 1] - lo, i0 = pc.y;
+    stage_costs(cost_sum + lo, n, cs);
+    __syncthreads();
+    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), nw = blockDim.x / WAVE;
+    const int n4 = (n + 3) & ~3, share = (n4 / 4 + nw - 1) / nw * 4;
+    const int i = i0 + lane;
+    const float ci = i < n ? cs[i] : 0.f;
+    part[w][lane] = rank_count(cs, w * share, min((w + 1) * share, n4), i, i0, min(i0 + RANK_CHUNK, n4), ci);
+    __syncthreads();
+    if (w > 0 || i >= n) return;
+    int r = 0;
+    for (int k = 0; k < nw; ++k) r += part[k][lane];
+    if (rank) rank[lo + i] = r;
+    if (order) order[lo + r] = lo + i;
+    if (elite_start && r < elite_count(n, elite_frac)) {
+        if (elite0) elite0[elite_start[pc.x] + r] = lo + i;
+        if (elite1) elite1[elite_start[pc.x] + r] = lo + i;
+    }
 }
 
-// one block per group; sorts by (cost, index), then copies and perturbs
-__global__ __launch_bounds__(1024) void k_resample(Consts P, ResampleArgs R, const int32_t *__restrict__ group_start,
-                                                   uint32_t window_idx, float *__restrict__ cost_sum,
-                                                   float *__restrict__ state, float *__restrict__ params,
-                                                   float *__restrict__ warm, int32_t *__restrict__ parent)
+// Copies and exploration.  ONE: a workgroup takes a whole group of at most
+// RESAMPLE_ONE simulations and ranks it first, four threads per simulation;
+// otherwise a workgroup takes COPY_CHUNK simulations of a group that k_rank
+// has ranked.  The parents are elites, which nothing here writes, so the
+// copies need no order among themselves; the running costs (read by the
+// ranking alone) are cleared.  Bound by the copies' latency and, for large
+// populations, their bytes: 16 groups of 1024 with 64-slot warm caches (13 MB
+// copied) take 53 us in one workgroup per group, 8 + 10 us like this; one
+// group of 16384 777 and 46; a group of 256 is 3 us faster in one workgroup
+// (one launch) than in two kernels.
+template <bool ONE>
+__global__ __launch_bounds__(1024) void k_resample(Consts P, ResampleArgs R, const int2 *__restrict__ piece,
+                                                   const int32_t *__restrict__ group_start, uint32_t window_idx,
+                                                   float *__restrict__ cost_sum, const int32_t *__restrict__ rank,
+                                                   const int32_t *__restrict__ order, float *__restrict__ state,
+                                                   float *__restrict__ params, float *__restrict__ warm,
+                                                   int32_t *__restrict__ parent)
 {
-    extern __shared__ __align__(16) char smem[];
-    const int g = blockIdx.x;
-    const int lo = group_start[g], hi = group_start[g + 1];
-    const int n = hi - lo;
-    const int np2 = sort_slots(n);
-    float *cs = reinterpret_cast<float *>(smem);
-    int *order = reinterpret_cast<int *>(smem + 4 * (size_t)np2);
-    sort_group(cost_sum + lo, n, np2, cs, order);
+    constexpr int M = ONE ? RESAMPLE_ONE : COPY_CHUNK;
+    __shared__ __align__(16) float cs[ONE ? RESAMPLE_ONE : 4];
+    __shared__ int rk[M], ord[ONE ? RESAMPLE_ONE : 1], par[M];
+    const int tid = threadIdx.x, nt = blockDim.x;
+    const int g = ONE ? blockIdx.x : piece[blockIdx.x].x;
+    const int i0 = ONE ? 0 : piece[blockIdx.x].y;
+    const int lo = group_start[g], n = group_start[g + 1] - lo;
+    const int m = min(n - i0, M);   // simulations of this workgroup
     const int kb = elite_count(n, R.elite_frac);
-    const uint32_t key0 = (uint32_t)(R.seed & 0xffffffffu), key1 = (uint32_t)(R.seed >> 32);
-    const int K = P.K;
-    // parents by rank (the sorted costs' LDS is free after the sort); the
-    // parents are elites, never overwritten, so every copy below is
-    // independent of the others
-    int *par = reinterpret_cast<int *>(cs);
-    for (int t = threadIdx.x; t < n; t += blockDim.x) {
-        const int j = lo + order[t];
-        if (t < kb) {
-            if (parent) parent[j] = -1;
-            continue;
+    const size_t K = P.K;
+    if constexpr (ONE) {
+        stage_costs(cost_sum + lo, n, cs);
+        __syncthreads();
+        // four adjacent lanes per simulation, a quarter of the group each
+        const int n4 = (n + 3) & ~3, share = (n4 / 4 + 3) / 4 * 4, q = tid & 3;
+        for (int i = tid >> 2; i - (tid >> 2) < n; i += nt >> 2) {
+            int r = 0;
+            if (i < n)
+                for (int j = q * share; j < min((q + 1) * share, n); ++j)
+                    r += cs[j] < cs[i] || (cs[j] == cs[i] && j < i) ? 1 : 0;
+            r += __shfl_xor(r, 1);
+            r += __shfl_xor(r, 2);
+            if (q == 0 && i < n) {
+                rk[i] = r;
+                ord[r] = lo + i;
+            }
         }
-        uint32_t w[4];
-        philox4x32_10((uint32_t)j, window_idx, 0u, 0u, key0, key1, w);
-        const int prank = (int)(((uint64_t)w[0] * (uint64_t)kb) >> 32);
-        const int p = lo + order[prank];
-        par[t] = p;
+        __syncthreads();
+    }
+    for (int s = tid; s < m; s += nt) {
+        const int j = lo + i0 + s, t = ONE ? rk[s] : rank[j];
+        int p = -1;
+        if (t >= kb) {
+            uint32_t w[4];
+            philox4x32_10((uint32_t)j, window_idx, 0u, 0u, (uint32_t)(R.seed & 0xffffffffu), (uint32_t)(R.seed >> 32), w);
+            const int prank = (int)(((uint64_t)w[0] * (uint64_t)kb) >> 32);
+            p = ONE ? ord[prank] : order[lo + prank];
+        }
+        par[s] = p;
         if (parent) parent[j] = p;
-        float e[5];
-        explore(R, (uint32_t)j, window_idx, params[0 * (size_t)K + p], params[1 * (size_t)K + p], e);
-        for (int c = 0; c < 5; ++c) params[(size_t)c * K + j] = e[c];
     }
     __syncthreads();
-    // state rows and warm-cache slots, one (simulation, row or slot) per
-    // thread, four of them loaded before any is stored (the copies read only
-    // elites, which nothing here writes)
-    const int nr = n - kb;
-    const int nt = blockDim.x;
-    for (int i0 = threadIdx.x; i0 < nr * 13; i0 += 4 * nt) {
-        const int i1 = i0 + nt, i2 = i0 + 2 * nt, i3 = i0 + 3 * nt;
-        const float v0 = state_row_src(state, K, kb, par, nr, i0);
-        const float v1 = state_row_src(state, K, kb, par, nr, i1);
-        const float v2 = state_row_src(state, K, kb, par, nr, i2);
-        const float v3 = state_row_src(state, K, kb, par, nr, i3);
-        state_row_dst(state, K, lo, kb, order, nr, i0, v0);
-        state_row_dst(state, K, lo, kb, order, nr, i1, v1);
-        state_row_dst(state, K, lo, kb, order, nr, i2, v2);
-        state_row_dst(state, K, lo, kb, order, nr, i3, v3);
+    // exploration by the block's last wavefronts, copies by the others: the
+    // draws are a chain as long as a wavefront's share of the copies
+    const int nx = (min(m, nt / 2) + WAVE - 1) / WAVE * WAVE, nc = nt > nx ? nt - nx : nt;
+    if (tid >= nt - nx) {
+        for (int s = tid - (nt - nx); s < m; s += nx) {
+            const int j = lo + i0 + s, p = par[s];
+            cost_sum[j] = 0.f;
+            if (p < 0) continue;
+            float e[5];
+            explore(R, (uint32_t)j, window_idx, params[p], params[K + p], e);
+            for (int c = 0; c < 5; ++c) params[(size_t)c * K + j] = e[c];
+        }
+        if (nc < nt) return;
     }
+    // warm-cache slots, four of a thread's loaded before any is stored
     float4 *w4 = reinterpret_cast<float4 *>(warm);
     const int C = P.C_max;
-    for (int i0 = threadIdx.x; i0 < nr * C; i0 += 4 * nt) {
-        const int i1 = i0 + nt, i2 = i0 + 2 * nt, i3 = i0 + 3 * nt;
-        const float4 v0 = warm_slot_src(w4, C, kb, par, nr, i0);
-        const float4 v1 = warm_slot_src(w4, C, kb, par, nr, i1);
-        const float4 v2 = warm_slot_src(w4, C, kb, par, nr, i2);
-        const float4 v3 = warm_slot_src(w4, C, kb, par, nr, i3);
-        warm_slot_dst(w4, C, lo, kb, order, nr, i0, v0);
-        warm_slot_dst(w4, C, lo, kb, order, nr, i1, v1);
-        warm_slot_dst(w4, C, lo, kb, order, nr, i2, v2);
-        warm_slot_dst(w4, C, lo, kb, order, nr, i3, v3);
+    const int items = m * C;
+    auto source = [&](int x) {
+        const int s = min(x, items - 1) / C, p = par[s];
+        return w4[(size_t)(p < 0 ? lo + i0 + s : p) * C + (min(x, items - 1) - s * C)];
+    };
+    auto copy = [&](int x, const float4 &v) {
+        if (x < items && par[x / C] >= 0) w4[(size_t)(lo + i0) * C + x] = v;
+    };
+    for (int x = tid; x < items; x += 4 * nc) {
+        const float4 a = source(x), b = source(x + nc), c = source(x + 2 * nc), d = source(x + 3 * nc);
+        copy(x, a);
+        copy(x + nc, b);
+        copy(x + 2 * nc, c);
+        copy(x + 3 * nc, d);
     }
-    for (int i = threadIdx.x; i < n; i += blockDim.x) cost_sum[lo + i] = 0.f;
+    // state rows, a row's simulations in order
+    for (int x = tid; x < 13 * m; x += nc) {
+        const int c = x / m, s = x - c * m, p = par[s];
+        if (p >= 0) state[(size_t)c * K + lo + i0 + s] = state[(size_t)c * K + p];
+    }
 }
 
 // ---------------------------------------------------------------------
@@ -726,13 +765,32 @@ hipError_t launch_argmin(int G, const int32_t *group_start, const float *cost, i
     return hipGetLastError();
 }
 
-hipError_t launch_resample(const Consts &P, const ResampleArgs &R, const int32_t *group_start, int max_group,
-                           uint32_t window_idx, float *cost_sum, float *state, float *params, float *warm,
-                           int32_t *parent, hipStream_t s)
+hipError_t launch_rank(const Pieces &rank_pieces, int max_group, float elite_frac, const int32_t *group_start,
+                       const int32_t *elite_start, const float *cost_sum, int32_t *rank, int32_t *order,
+                       int32_t *elite0, int32_t *elite1, hipStream_t s)
 {
-    size_t lds = resample_lds_bytes(max_group);
-    hipLaunchKernelGGL(k_resample, dim3(P.G), dim3(group_threads(max_group)), lds, s, P, R, group_start, window_idx,
-                       cost_sum, state, params, warm, parent);
+    const int waves = std::min(16, (max_group + WAVE - 1) / WAVE);
+    hipLaunchKernelGGL(k_rank, dim3(rank_pieces.count), dim3(WAVE * waves), sizeof(float) * ((max_group + 3) & ~3), s,
+                       elite_frac, rank_pieces.piece, group_start, elite_start, cost_sum, rank, order, elite0, elite1);
+    return hipGetLastError();
+}
+
+hipError_t launch_resample(const Consts &P, const ResampleArgs &R, const int32_t *group_start, int max_group,
+                           const Pieces &rank_pieces, const Pieces &copy_pieces, uint32_t window_idx, float *cost_sum,
+                           int32_t *rank, int32_t *order, float *state, float *params, float *warm, int32_t *parent,
+                           hipStream_t s)
+{
+    if (max_group <= RESAMPLE_ONE) {
+        const int threads = std::max(256, std::min(1024, (4 * max_group + WAVE - 1) / WAVE * WAVE));
+        hipLaunchKernelGGL(k_resample<true>, dim3(P.G), dim3(threads), 0, s, P, R, nullptr, group_start, window_idx,
+                           cost_sum, nullptr, nullptr, state, params, warm, parent);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_rank(rank_pieces, max_group, R.elite_frac, group_start, nullptr, cost_sum, rank, order,
+                               nullptr, nullptr, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_resample<false>, dim3(copy_pieces.count), dim3(256), 0, s, P, R, copy_pieces.piece, group_start,
+                       window_idx, cost_sum, rank, order, state, params, warm, parent);
     return hipGetLastError();
 }
 
@@ -794,7 +852,7 @@ hipError_t set_lds_limits(size_t bytes)
                         reinterpret_cast<const void *>(k_step<float, true>),
                         reinterpret_cast<const void *>(k_step<double, true>),
                         reinterpret_cast<const void *>(k_step<double, false, true>),
-                        reinterpret_cast<const void *>(k_resample)};
+                        reinterpret_cast<const void *>(k_rank)};
     for (const void *f : fs) {
         hipError_t e = set_dynamic_lds_limit(f, bytes);
         if (e != hipSuccess) return e;
