@@ -268,8 +268,8 @@ PT_API pt_status pt_resample_wrs(pt_batch b, float *cost_sum, int32_t n_steps, u
  * costs, eta* = argmin over eta > 0 of eta epsilon + eta log((1/K_f) sum_i
  * exp(R_i / eta)) (K_f finite costs), P(i) = softmax(R_i / eta*); then the
  * draw, copies and exploration of pt_resample_wrs.  eta* is found where the
- * dual's slope epsilon - KL(P_eta || uniform) vanishes, by bisection on
- * log(eta) to ~1e-13; when all finite costs are equal P is uniform over
+ * dual's slope epsilon - KL(P_eta || uniform) vanishes, by Newton's method
+ * on log(eta), bracketed, to ~1e-13; when all finite costs are equal P is uniform over
  * them, and with no finite cost uniform over the group (eta* reported as
  * +inf in both cases); when epsilon >= log(K_f / #argmin) the
  * dual has no interior minimum and P is the eta -> 0+ limit, uniform over

@@ -2,8 +2,8 @@
 // (Sec. III-D.1 WRS, Eq. 4; Sec. III-D.2 REPS, Eqs. 5-6) for gfx950.
 //
 //   k_weighted_draw   one workgroup per group: window-mean costs, the
-//                     temperature (fixed for WRS; REPS: bisection on the
-//                     dual's optimality condition), the weights, their
+//                     temperature (fixed for WRS; REPS: bracketed Newton on
+//                     the dual's optimality condition), the weights, their
 //                     running sum in LDS and one categorical draw per
 //                     simulation (Philox counter (j, window, 3, 0))
 //   k_gather          snapshot of every simulation's parent (state, params,
@@ -18,37 +18,51 @@
 
 namespace pt {
 
+// threads of a group's workgroup: REPS's uniform arithmetic (logarithms and
+// divisions, as much as an evaluation's work on four simulations) is done by
+// every wavefront, so small groups take few of them (16 groups of 1024: 256
+// threads 26 us, 1024 threads 37 us); past DRAW_SMALL the draws'
+// searches, a chain of LDS reads each, want as many as there are
 constexpr int DRAW_THREADS = 1024;
-constexpr int DRAW_WAVES = DRAW_THREADS / WAVE;
-constexpr int REPS_BISECTIONS = 48;     // log(eta) bracket of width 60 -> 2e-13
+constexpr int DRAW_THREADS_SMALL = 256;
+constexpr int DRAW_SMALL = 2048;
+constexpr int DRAW_WAVES = DRAW_THREADS / WAVE;   // at most
+// REPS's temperature: Newton steps until one is below REPS_TOL in log(eta),
+// then a bisection of the bracket (width 60) for a function that will not
+// converge; together at most REPS_NEWTON + REPS_BISECTIONS evaluations
+constexpr double REPS_TOL = 1e-13;
+constexpr int REPS_NEWTON = 24;
+constexpr int REPS_BISECTIONS = 48;     // 60 / 2^48 = 2e-13
+
+// place of entry i in the group's LDS array: one word of padding every 16, so
+// that the threads' chunks (up to 16 entries each) start on different banks
+// (one group of 16384: WRS 97 us without, 76 us with)
+__host__ __device__ constexpr int draw_at(int i) { return i + (i >> 4); }
 
 // block-wide sums and extrema of doubles (every thread gets the result)
 struct DrawLds {
-    double red[2][DRAW_WAVES * 2];
+    double red[2][DRAW_WAVES * 3];
     int ired[DRAW_WAVES * 2];
 };
 
-__device__ __forceinline__ double wave_sum_d(double v)
-{
-#pragma unroll
-    for (int off = WAVE / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
-// sums of (a, b) over the block; `phase` alternates the LDS slot so that
+// sums of three values over the block: per wavefront by DPP, the wavefronts'
+// sums by DPP again (one lane each); `phase` alternates the LDS slot so that
 // consecutive calls need one barrier each
-__device__ __forceinline__ void block_sum2(double &a, double &b, DrawLds &L, int phase)
+template <int NT>
+__device__ __forceinline__ void block_sum3(double (&v)[3], DrawLds &L, int phase)
 {
-    const int w = threadIdx.x / WAVE;
-    a = wave_sum_d(a);
-    b = wave_sum_d(b);
+    static_assert(DRAW_WAVES == 16, "one DPP row of wavefronts");
+    const int w = threadIdx.x / WAVE, lane = lane_id();
+    wave_sum<double, 3>(v);
     double *r = L.red[phase & 1];
-    if (lane_id() == 0) { r[2 * w] = a; r[2 * w + 1] = b; }
+    if (lane == 0) { r[w] = v[0]; r[DRAW_WAVES + w] = v[1]; r[2 * DRAW_WAVES + w] = v[2]; }
     __syncthreads();
-    a = 0.0; b = 0.0;
-    for (int k = 0; k < DRAW_WAVES; ++k) { a += r[2 * k]; b += r[2 * k + 1]; }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[k] = lane < NT / WAVE ? r[k * DRAW_WAVES + lane] : 0.0;
+    wave_sum<double, 3>(v, DRAW_WAVES);
 }
 
+template <int NT>
 __device__ __forceinline__ void block_minmax(double &lo, double &hi, DrawLds &L)
 {
     const int w = threadIdx.x / WAVE;
@@ -60,10 +74,11 @@ __device__ __forceinline__ void block_minmax(double &lo, double &hi, DrawLds &L)
     __syncthreads();
     if (lane_id() == 0) { L.red[0][2 * w] = lo; L.red[0][2 * w + 1] = hi; }
     __syncthreads();
-    for (int k = 0; k < DRAW_WAVES; ++k) { lo = fmin(lo, L.red[0][2 * k]); hi = fmax(hi, L.red[0][2 * k + 1]); }
+    for (int k = 0; k < NT / WAVE; ++k) { lo = fmin(lo, L.red[0][2 * k]); hi = fmax(hi, L.red[0][2 * k + 1]); }
     __syncthreads();
 }
 
+template <int NT>
 __device__ __forceinline__ void block_isum2(int &a, int &b, DrawLds &L)
 {
     const int w = threadIdx.x / WAVE;
@@ -76,7 +91,7 @@ __device__ __forceinline__ void block_isum2(int &a, int &b, DrawLds &L)
     if (lane_id() == 0) { L.ired[2 * w] = a; L.ired[2 * w + 1] = b; }
     __syncthreads();
     a = 0; int m = -1;
-    for (int k = 0; k < DRAW_WAVES; ++k) { a += L.ired[2 * k]; m = max(m, L.ired[2 * k + 1]); }
+    for (int k = 0; k < NT / WAVE; ++k) { a += L.ired[2 * k]; m = max(m, L.ired[2 * k + 1]); }
     b = m;
     __syncthreads();
 }
@@ -87,7 +102,8 @@ __device__ __forceinline__ void block_isum2(int &a, int &b, DrawLds &L)
 // weights (they sum to 1 over the group) and REPS's eta* (0: the limit
 // eta -> 0+, uniform over the lowest costs; +inf: all finite costs equal,
 // or none finite).
-__global__ __launch_bounds__(DRAW_THREADS) void k_weighted_draw(int kind, float hyper, const int32_t *__restrict__ group_start,
+template <int NT>
+__global__ __launch_bounds__(NT) void k_weighted_draw(int kind, float hyper, const int32_t *__restrict__ group_start,
                                                                 const float *__restrict__ cost_sum, int n_steps,
                                                                 uint32_t window_idx, uint64_t seed,
                                                                 float *__restrict__ weights, float *__restrict__ eta_out,
@@ -100,7 +116,7 @@ __global__ __launch_bounds__(DRAW_THREADS) void k_weighted_draw(int kind, float 
     const int lo = group_start[g], hi = group_start[g + 1];
     const int n = hi - lo;
     if (n <= 0) return;
-    const int ch = (n + DRAW_THREADS - 1) / DRAW_THREADS;
+    const int ch = (n + NT - 1) / NT;
     const int i0 = threadIdx.x * ch;
     const double inv_steps = 1.0 / (double)n_steps;
 
@@ -112,24 +128,24 @@ __global__ __launch_bounds__(DRAW_THREADS) void k_weighted_draw(int kind, float 
     const int i1 = min(i0 + ch, n);
     for (int i = i0; i < i1; ++i) {
         const double ci = (double)cost_sum[lo + i] * inv_steps;
-        cdf[i] = ci;
+        cdf[draw_at(i)] = ci;
         if (isfinite(ci)) {
             cmin = fmin(cmin, ci);
             cmax = fmax(cmax, ci);
         }
     }
-    block_minmax(cmin, cmax, L);
+    block_minmax<NT>(cmin, cmax, L);
     int nf = 0, nmin = 0;
     for (int i = i0; i < i1; ++i) {
-        const double ci = cdf[i];
+        const double ci = cdf[draw_at(i)];
         if (isfinite(ci)) { ++nf; nmin += ci == cmin ? 1 : 0; }
     }
     {
         int a = nf, b = -1;
-        block_isum2(a, b, L);
+        block_isum2<NT>(a, b, L);
         nf = a;
         int m = nmin, d = -1;
-        block_isum2(m, d, L);
+        block_isum2<NT>(m, d, L);
         nmin = m;
     }
 
@@ -154,33 +170,53 @@ __global__ __launch_bounds__(DRAW_THREADS) void k_weighted_draw(int kind, float 
             // KL(P_eta || uniform) = log nf - log Z - S1 / (eta Z), with
             // Z = sum exp(-(c - cmin) / eta), S1 = sum (c - cmin) exp(...);
             // it falls as eta grows, and the dual's minimiser is where it
-            // equals eps (below spread / eps, where KL <= spread / eta <= eps)
-            double thi = log(spread / eps), tlo = thi - 60.0;
-            for (int it = 0; it < REPS_BISECTIONS; ++it) {
-                const double tm = 0.5 * (tlo + thi);
+            // equals eps (below spread / eps, where KL <= spread / eta <= eps).
+            // In t = log(eta) its derivative is -Var / eta^2, Var the variance
+            // of c under P, and log KL is a line of slope -2 where eta is
+            // large: Newton on log(KL / eps) from the bracket's upper end
+            // takes 5 to 8 evaluations where bisection takes 48, a step
+            // that leaves the bracket is replaced by its middle.  Each
+            // evaluation is one exp per simulation, two levels of DPP sums
+            // and a barrier, ~2 us; 16 groups of 1024: 140 us with the
+            // bisection, 26 us with Newton.
+            double thi = log(spread / eps), tlo = thi - 60.0, tm = thi;
+            const double lnf = log((double)nf);
+            bool done = false;
+            for (int it = 0; it < REPS_NEWTON + REPS_BISECTIONS && !done; ++it) {
                 const double ie = exp(-tm);
-                double z = 0.0, s1 = 0.0;
+                double v[3] = {0.0, 0.0, 0.0};   // Z, S1, S2
                 for (int i = i0; i < i1; ++i) {
-                    const double ci = cdf[i];
+                    const double ci = cdf[draw_at(i)];
                     if (isfinite(ci)) {
                         const double d = ci - cmin;
-                        const double x = exp(-d * ie);
-                        z += x;
-                        s1 += d * x;
+                        const double x = exp(-d * ie), dx = d * x;
+                        v[0] += x;
+                        v[1] += dx;
+                        v[2] += d * dx;
                     }
                 }
-                block_sum2(z, s1, L, it);
-                const double kl = log((double)nf) - log(z) - s1 * ie / z;
+                block_sum3<NT>(v, L, it);
+                const double mean = v[1] / v[0], var = v[2] / v[0] - mean * mean;
+                const double kl = lnf - log(v[0]) - mean * ie;
                 if (kl > eps) tlo = tm; else thi = tm;
+                // the root may lie on the bracket's end to rounding: a step
+                // below the tolerance ends the search wherever it goes
+                const double step = log(kl / eps) * kl / (ie * ie * var);
+                double tn = tm + step;
+                done = fabs(step) <= REPS_TOL;
+                if (!done && (it >= REPS_NEWTON || !(tn > tlo && tn < thi))) {
+                    tn = 0.5 * (tlo + thi);
+                    done = thi - tlo <= REPS_TOL;
+                }
+                tm = tn;
             }
-            eta = exp(0.5 * (tlo + thi));
+            eta = exp(tm);
             lam = 1.0 / eta;
         }
     }
 
-    // weights of the chunk and their running sum (inclusive) through the
-    // block: chunk sums scanned over the threads (the weights are formed
-    // twice, for the chunk sum and for the running sum)
+    // weights of the chunk (in place of its means) and their running sum
+    // (inclusive) through the block: chunk sums scanned over the threads
     auto weight = [&](double ci) -> double {
         if (mode == UNIFORM_ALL) return 1.0;
         if (!isfinite(ci)) return 0.0;
@@ -191,7 +227,8 @@ __global__ __launch_bounds__(DRAW_THREADS) void k_weighted_draw(int kind, float 
     double tsum = 0.0;
     int last = -1;
     for (int i = i0; i < i1; ++i) {
-        const double wi = weight(cdf[i]);
+        const double wi = weight(cdf[draw_at(i)]);
+        cdf[draw_at(i)] = wi;
         if (wi > 0.0) last = i;
         tsum += wi;
     }
@@ -208,21 +245,21 @@ __global__ __launch_bounds__(DRAW_THREADS) void k_weighted_draw(int kind, float 
     if (lane == WAVE - 1) L.red[0][wv] = incl;
     __syncthreads();
     double base = 0.0, total = 0.0;
-    for (int k = 0; k < DRAW_WAVES; ++k) {
+    for (int k = 0; k < NT / WAVE; ++k) {
         const double t = L.red[0][k];
         if (k < wv) base += t;
         total += t;
     }
     double run = base + (incl - tsum);
     for (int i = i0; i < i1; ++i) {
-        const double wi = weight(cdf[i]);
+        const double wi = cdf[draw_at(i)];
         run += wi;
-        cdf[i] = run;
+        cdf[draw_at(i)] = run;
         if (weights) weights[lo + i] = (float)(wi / total);
     }
     {
         int a = 0, b = last;
-        block_isum2(a, b, L);
+        block_isum2<NT>(a, b, L);
         last = b;
     }
     if (eta_out && threadIdx.x == 0) eta_out[g] = kind == 1 ? (float)eta : 0.f;
@@ -231,7 +268,7 @@ __global__ __launch_bounds__(DRAW_THREADS) void k_weighted_draw(int kind, float 
     // one draw per simulation: the first index whose running sum exceeds
     // u * total, u = (w0 + 1/2) 2^-32
     const uint32_t key0 = (uint32_t)(seed & 0xffffffffu), key1 = (uint32_t)(seed >> 32);
-    for (int i = threadIdx.x; i < n; i += DRAW_THREADS) {
+    for (int i = threadIdx.x; i < n; i += NT) {
         const int j = lo + i;
         uint32_t r[4];
         philox4x32_10((uint32_t)j, window_idx, 3u, 0u, key0, key1, r);
@@ -239,7 +276,7 @@ __global__ __launch_bounds__(DRAW_THREADS) void k_weighted_draw(int kind, float 
         int a = 0, b = n;                    // first index in [a, b) with cdf > t
         while (a < b) {
             const int m = (a + b) >> 1;
-            if (cdf[m] > t) b = m; else a = m + 1;
+            if (cdf[draw_at(m)] > t) b = m; else a = m + 1;
         }
         parent[j] = lo + (a < last ? a : last);
     }
@@ -299,15 +336,19 @@ __global__ __launch_bounds__(256) void k_apply(int K, int C_max, ResampleArgs R,
 
 using namespace pt;
 
-size_t weighted_draw_lds_bytes(int max_group) { return (size_t)8 * (size_t)max_group; }
+size_t weighted_draw_lds_bytes(int max_group) { return (size_t)8 * (size_t)draw_at(max_group); }
 
 hipError_t launch_weighted_resample(const Consts &P, const ResampleArgs &R, int kind, float hyper,
                                     const int32_t *group_start, int max_group, int n_steps, uint32_t window_idx,
                                     float *cost_sum, float *state, float *params, float *warm, float *snap,
                                     int32_t *parent, float *weights, float *eta, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_weighted_draw, dim3(P.G), dim3(DRAW_THREADS), weighted_draw_lds_bytes(max_group), s, kind,
-                       hyper, group_start, cost_sum, n_steps, window_idx, R.seed, weights, eta, parent);
+    auto draw = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3(P.G), dim3(threads), weighted_draw_lds_bytes(max_group), s, kind, hyper,
+                           group_start, cost_sum, n_steps, window_idx, R.seed, weights, eta, parent);
+    };
+    max_group <= DRAW_SMALL ? draw(k_weighted_draw<DRAW_THREADS_SMALL>, DRAW_THREADS_SMALL)
+                            : draw(k_weighted_draw<DRAW_THREADS>, DRAW_THREADS);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t total = (size_t)18 * P.K + (size_t)P.K * P.C_max;
@@ -322,5 +363,5 @@ hipError_t launch_weighted_resample(const Consts &P, const ResampleArgs &R, int 
 
 hipError_t set_draw_lds_limits(size_t bytes)
 {
-    return set_dynamic_lds_limit(reinterpret_cast<const void *>(k_weighted_draw), bytes);
+    return set_dynamic_lds_limit(reinterpret_cast<const void *>(k_weighted_draw<DRAW_THREADS>), bytes);
 }
