@@ -396,11 +396,11 @@ pt_status pt_create_batch(const pt_batch_desc *d, pt_batch *out)
     if (st != PT_OK) return st;
     // candidate list (every sphere-link pair up to pt::CAND_CAP entries -- a
     // step with more cuts its list to the C_max lowest and goes on); the same
-    // LDS holds, once the cap has run, the rows of the solve's cross-contact sums
-    // (rows of RedStride<double> = 44 doubles: one per contact slot for the
-    // PD solve's per-link sums, at most 32 for the kinematic solve's sums,
-    // which fold the upper half-wave's contacts onto the lower one's)
-    const int red_rows = d->C_max <= 16 ? 16 : (d->C_max <= 32 || d->hand_mode == 0 ? 32 : 64);
+    // LDS holds, once the cap has run, the rows of the solve's cross-contact
+    // sums: at most 32 of RedStride<double> = 44 doubles for the kinematic
+    // solve, which folds the upper half-wave's contacts onto the lower one's;
+    // pt::PD_ROWS of them and a row per run of contacts for the PD solve's
+    // per-link sums
     // the PD hand's structure
     std::vector<int32_t> pd_tab;
     int pd_groups = 0, pd_dmax = 0, pd_gmax = 0;
@@ -411,12 +411,13 @@ pt_status pt_create_batch(const pt_batch_desc *d, pt_batch *out)
     // ... and the step's hand kinematics, which use the same LDS first
     const size_t fk_bytes = d->hand_mode == 1 ? pt::pd_fk_bytes(d->L) : hand_fk_lds_bytes(d->L, d->D);
     const int n_pairs = d->collision_mode == 1 ? d->L * d->link_samples + d->S_max : d->S_max * (d->L + 1);
-    const int list = std::min(n_pairs, pt::CAND_CAP), rows = red_rows * pt::RedStride<double>::value,
-              fk = (int)((fk_bytes + 7) / 8);
+    const int list = std::min(n_pairs, pt::CAND_CAP), fk = (int)((fk_bytes + 7) / 8);
+    const int rows = d->hand_mode == 1 ? pt::pd_sum_doubles(d->C_max, d->L)
+                                       : (d->C_max <= 16 ? 16 : 32) * pt::RedStride<double>::value;
     int max_cand, max_cand_rows;
     if (d->hand_mode == 1) {
         // the PD solve keeps its group solutions in the spare words
-        max_cand = std::max({round_up(list, 64), round_up(rows, 64), round_up(fk, 64)});
+        max_cand = std::max({round_up(list, 4), round_up(rows, 4), round_up(fk, 4)});
         max_cand_rows = max_cand;
     } else {
         // the sum rows may run on into the spare words after a shorter
@@ -426,7 +427,7 @@ pt_status pt_create_batch(const pt_batch_desc *d, pt_batch *out)
         max_cand_rows = std::max(max_cand, round_up(rows, 32));
     }
     const size_t wave_lds = std::max(pt::wave_lds_bytes(max_cand, d->L), pt::wave_lds_bytes(max_cand_rows, 0)) +
-                            (d->hand_mode == 1 ? pt::pd_lds_bytes(d->D) : 0);
+                            (d->hand_mode == 1 ? pt::pd_lds_bytes(d->L, d->D) : 0);
     if (wave_lds > 160 * 1024)
         return fail(PT_E_UNSUPPORTED, "%zu B of LDS per simulation (> 160 KiB)", wave_lds);
 

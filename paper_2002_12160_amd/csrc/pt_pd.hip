@@ -35,7 +35,7 @@ __global__ __launch_bounds__(WAVE) void k_step_pd(Consts P, PdConsts Q, Tables t
     const int D = P.D;
     const size_t K = P.K;
     WaveLds lds = carve_lds(smem, 0, P.max_cand, P.L);
-    const PdLds pl = carve_pd(smem + wave_lds_bytes(P.max_cand, P.L), D, lds.sel);
+    const PdLds pl = carve_pd(smem + wave_lds_bytes(P.max_cand, P.L), P.L, D, lds);
     const int type = tb.env_type[e];
     const int S = tb.n_spheres[type];
     const float *sph = tb.spheres + (size_t)type * P.S_max * 4;
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(WAVE) void k_window_pd(Consts P, PdConsts Q, Tables
     const int D = P.D;
     const size_t K = P.K;
     WaveLds lds = carve_lds(smem, 0, P.max_cand, P.L);
-    const PdLds pl = carve_pd(smem + wave_lds_bytes(P.max_cand, P.L), D, lds.sel);
+    const PdLds pl = carve_pd(smem + wave_lds_bytes(P.max_cand, P.L), P.L, D, lds);
     float *stage = contact_stage(lds);
     // the joint angles by row for the cost (the cap's slots are free by then)
     float *qrow = reinterpret_cast<float *>(lds.sel);
@@ -245,7 +245,7 @@ __global__ __launch_bounds__(256) void k_copy_hand(int K, int rows, const int32_
 
 using namespace pt;
 
-size_t pd_wave_lds_bytes(int max_cand, int L, int D) { return wave_lds_bytes(max_cand, L) + pd_lds_bytes(D); }
+size_t pd_wave_lds_bytes(int max_cand, int L, int D) { return wave_lds_bytes(max_cand, L) + pd_lds_bytes(L, D); }
 
 hipError_t set_pd_lds_limits(size_t bytes)
 {

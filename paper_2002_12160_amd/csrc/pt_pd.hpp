@@ -81,36 +81,57 @@ __host__ __device__ constexpr size_t pd_tab_ints(int L, int D, int groups)
     return (size_t)6 * D + L + (size_t)L * PD_CHAIN + groups + 1;
 }
 
+// The contact sums go through LDS PD_ROWS contacts at a time, in the
+// candidate list's words (free once the cap has run): PD_ROWS rows of
+// RedStride<double>, then one row of PD_SUM per run of contacts on one link.
+// All 64 rows at once would take 22 KB, five wavefronts per compute unit on
+// the real-time hand (20 links, 20 joints); 16 rows and 21 sums fit in the
+// list's 12.3 KB, which leaves the registers as the limit (eight).
+constexpr int PD_ROWS = 16;
+constexpr int PD_SUM = 42;
+
+// runs of contacts, at most (the links, and the table)
+__host__ __device__ constexpr int pd_max_runs(int C_max, int L) { return C_max < L + 1 ? C_max : L + 1; }
+
+// words of the candidate list the sums need
+__host__ __device__ constexpr int pd_sum_doubles(int C_max, int L)
+{
+    return PD_ROWS * RedStride<double>::value + PD_SUM * pd_max_runs(C_max, L);
+}
+
 // per-wave LDS of the PD step (after the kinematic path's WaveLds)
 struct PdLds {
     double *S;      // [D][6] joint twists about the object centre (first: origin, axis)
     double *Ah;     // [D][PD_GMAX] rows of A_h's group blocks
     double *pm;     // [D] M qdot + dt kp (u - q)
     double *Aoh;    // [D][6] column p of A_oh
-    double *Aho;    // [D][6] row p of A_ho
+    double *Aho;    // [D][6] row p of A_ho (first: the joints' half-angle sines and cosines)
     double *bh;     // [D]
     double *X;      // [D][PD_GMAX]
     double *Y;      // [D][PD_YS]
     double *zh;     // [D] hand part of the Newton direction (first: q staged)
     double *nuh;    // [D] joint rates (first: qdot staged)
-    double *tot;    // [48] sums over all contacts
-    double *acc;    // [48] the object's reduced system
-    int *rowlink;   // [64] link of each row of the ordered contacts
-    int *linkrow;   // [64] first row of each link's run of rows (-1: no contact on the link)
+    double *rows;   // [PD_ROWS][RedStride] the sums' rows; between them: tot, acc
+    double *sums;   // [runs][PD_SUM] sums over each run of contacts
+    double *tot;    // [48] sums over all contacts (in rows, after the last pass)
+    double *acc;    // [48] the object's reduced system (in rows)
+    int *linkrun;   // [64] run of each link (-1: no contact on the link)
 };
 
 // Up to PD_SPARE_D joints the group solve's X and Y live in the wave's cap
 // slots, warm-cache lookup and contact stage (sel .. the stage's end, 576
-// words), which nothing reads between the warm start and the integration:
-// on the real-time hand (D = 20) that keeps the wave under 32 KiB, five
-// wavefronts per compute unit instead of four.
+// words), which nothing reads between the warm start and the integration.
 constexpr int PD_SPARE_WORDS = 9 * 64;
 constexpr int PD_SPARE_D = 4 * PD_SPARE_WORDS / (8 * (PD_GMAX + PD_YS));
 
-__host__ __device__ constexpr size_t pd_lds_bytes(int D)
+// A_oh lives in the hand's segment records (64 L bytes) where it fits: the
+// solve does not read them
+__host__ __device__ constexpr bool pd_aoh_in_seg(int L, int D) { return 48 * D <= 64 * L; }
+
+__host__ __device__ constexpr size_t pd_lds_bytes(int L, int D)
 {
-    return (size_t)8 * ((size_t)D * (6 + PD_GMAX + 1 + 6 + 6 + 1 + 1 + 1) + 96) +
-           (D <= PD_SPARE_D ? 0 : (size_t)8 * D * (PD_GMAX + PD_YS)) + (size_t)4 * (64 + 64);
+    return (size_t)8 * ((size_t)D * ((pd_aoh_in_seg(L, D) ? 0 : 6) + 6 + PD_GMAX + 1 + 6 + 1 + 1 + 1)) +
+           (D <= PD_SPARE_D ? 0 : (size_t)8 * D * (PD_GMAX + PD_YS)) + (size_t)4 * 64;
 }
 
 // LDS of the hand kinematics (in the candidate list, before the narrow
@@ -118,19 +139,23 @@ __host__ __device__ constexpr size_t pd_lds_bytes(int D)
 // and the world inertia
 __host__ __device__ constexpr size_t pd_fk_bytes(int L) { return (size_t)8 * 19 * L; }
 
-// p: the PD area after the wave's WaveLds; spare: that WaveLds's sel
-__device__ __forceinline__ PdLds carve_pd(char *p, int D, int *spare)
+// p: the PD area after the wave's WaveLds w
+__device__ __forceinline__ PdLds carve_pd(char *p, int L, int D, const WaveLds &w)
 {
     PdLds s;
     double *d = reinterpret_cast<double *>(p);
     s.S = d; d += 6 * D;
     s.Ah = d; d += PD_GMAX * D;
     s.pm = d; d += D;
-    s.Aoh = d; d += 6 * D;
+    if (pd_aoh_in_seg(L, D)) {
+        s.Aoh = reinterpret_cast<double *>(w.seg);
+    } else {
+        s.Aoh = d; d += 6 * D;
+    }
     s.Aho = d; d += 6 * D;
     s.bh = d; d += D;
     if (D <= PD_SPARE_D) {
-        s.X = reinterpret_cast<double *>(spare);
+        s.X = reinterpret_cast<double *>(w.sel);
         s.Y = s.X + PD_GMAX * D;
     } else {
         s.X = d; d += PD_GMAX * D;
@@ -138,13 +163,26 @@ __device__ __forceinline__ PdLds carve_pd(char *p, int D, int *spare)
     }
     s.zh = d; d += D;
     s.nuh = d; d += D;
-    s.tot = d; d += 48;
-    s.acc = d; d += 48;
-    int *i = reinterpret_cast<int *>(d);
-    s.rowlink = i; i += 64;
-    s.linkrow = i;
+    s.linkrun = reinterpret_cast<int *>(d);
+    s.rows = reinterpret_cast<double *>(w.cand_d);
+    s.sums = s.rows + PD_ROWS * RedStride<double>::value;
+    s.tot = s.rows;
+    s.acc = s.rows + 48;
     return s;
 }
+
+// What the lanes of a step need of the hand's structure, read from the table
+// (and the contacts' runs) once instead of in every Newton iteration, where
+// each look was a chain of memory accesses.
+// Lane tasks of the object-hand and hand-hand blocks: t = lane and lane + 64
+// (and on for hands of more than 21 joints).
+struct PdLane {
+    uint64_t chain;   // positions of the joints moving this lane's contact, a byte each from the
+                      // lowest (0xff: no more)
+    int g0, n;        // this lane's group in the group solves (lane / 7), n = 0: none
+    int x0, x1;       // its hand-hand tasks (0 and 1), see pd_hand_task
+    uint64_t r0, r1;  // the runs that the joints of its object-hand tasks (0 and 1) move
+};
 
 // Kinematics of the hand at the joint angles staged in pl.zh (by position),
 // link by link down the tree (links of one depth in parallel): per joint its
@@ -157,6 +195,14 @@ __device__ __forceinline__ void pd_fk(const Consts &P, const PdConsts &Q, const 
 {
     const int L = P.L, lane = lane_id();
     double *tq = fk, *tb = fk + 4 * L, *com = fk + 7 * L, *Iw = fk + 10 * L;
+    // the transcendental part for all joints at once
+    if (lane < P.D) {
+        double sn, cs;
+        sincos(0.5 * pl.zh[lane], &sn, &cs);
+        pl.Aho[2 * lane] = sn;
+        pl.Aho[2 * lane + 1] = cs;
+    }
+    wave_sync();
     for (int d = 0; d <= Q.dmax; ++d) {
         for (int l = lane; l < L; l += WAVE) {
             if (T.depth(l) != d) continue;
@@ -191,8 +237,7 @@ __device__ __forceinline__ void pd_fk(const Consts &P, const PdConsts &Q, const 
                     s[i] = o[i];
                     s[3 + i] = Rf[3 * i] * ax[0] + Rf[3 * i + 1] * ax[1] + Rf[3 * i + 2] * ax[2];
                 }
-                double sn, cs;
-                sincos(0.5 * pl.zh[p], &sn, &cs);
+                const double sn = pl.Aho[2 * p], cs = pl.Aho[2 * p + 1];
                 const double qj[4] = {cs, sn * ax[0], sn * ax[1], sn * ax[2]};
                 double t[4];
                 quat_mul_d(qf, qj, t);
@@ -248,43 +293,48 @@ __device__ __forceinline__ void pd_fk(const Consts &P, const PdConsts &Q, const 
     }
 }
 
-// The group blocks of A_h = M(q) + (dt kd + dt^2 kp) I and the momentum
-// pm = M qdot + dt kp (u - q), one lane per joint (joint rates staged in
-// pl.nuh by position).  M_ij sums over the links both joints move:
-// m v_i . v_j + a_j . Iw a_i with v_i = a_i x (com - o_i).
+// The group blocks of A_h = M(q) + (dt kd + dt^2 kp) I, one lane per entry,
+// and the momentum pm = M qdot + dt kp (u - q), one lane per joint (joint
+// rates staged in pl.nuh by position).  M_ij sums over the links both joints
+// move: m v_i . v_j + a_j . Iw a_i with v_i = a_i x (com - o_i).
 __device__ __forceinline__ void pd_mass(const Consts &P, const PdConsts &Q, const PdTab &T, const double *fk,
                                         const PdLds &pl, const float *__restrict__ u, const double q_lane)
 {
-    const int L = P.L, D = P.D, lane = lane_id();
+    const int L = P.L, D = P.D, lane = lane_here();
     const double *com = fk + 7 * L, *Iw = fk + 10 * L;
     const double dt = P.dt, cdiag = dt * (double)Q.kd + dt * dt * (double)Q.kp, ml = Q.link_mass;
-    if (lane < D) {
-        const int p = lane;
-        const int g0 = T.gs(p), n = T.gn(p);
-        const uint64_t sp = T.sub(p);
+    for (int t = lane; t < Q.gmax * D; t += WAVE) {
+        const int k = t / D, p = t - k * D;
+        if (k >= T.gn(p)) continue;
+        const int j = T.gs(p) + k;
         const double *op = pl.S + 6 * p, *ap = op + 3;
+        const double *oj = pl.S + 6 * j, *aj = oj + 3;
+        uint64_t in = T.sub(p) & T.sub(j);
+        double m = 0.0;
+        while (in) {
+            const int l = __builtin_ctzll(in);
+            in &= in - 1;
+            const double *c = com + 3 * l, *I = Iw + 9 * l;
+            const double ri[3] = {c[0] - op[0], c[1] - op[1], c[2] - op[2]};
+            const double rj[3] = {c[0] - oj[0], c[1] - oj[1], c[2] - oj[2]};
+            double vi[3], vj[3];
+            cross3(ap, ri, vi);
+            cross3(aj, rj, vj);
+            const double Ia[3] = {I[0] * ap[0] + I[1] * ap[1] + I[2] * ap[2],
+                                  I[3] * ap[0] + I[4] * ap[1] + I[5] * ap[2],
+                                  I[6] * ap[0] + I[7] * ap[1] + I[8] * ap[2]};
+            m += ml * dot3(vi, vj) + dot3(aj, Ia);
+        }
+        pl.Ah[PD_GMAX * p + k] = m;
+    }
+    wave_sync();
+    if (lane < D) {
+        const int p = lane, g0 = T.gs(p), n = T.gn(p);
         double mom = 0.0;
         for (int k = 0; k < n; ++k) {
-            const int j = g0 + k;
-            const double *oj = pl.S + 6 * j, *aj = oj + 3;
-            uint64_t in = sp & T.sub(j);
-            double m = 0.0;
-            while (in) {
-                const int l = __builtin_ctzll(in);
-                in &= in - 1;
-                const double *c = com + 3 * l, *I = Iw + 9 * l;
-                const double ri[3] = {c[0] - op[0], c[1] - op[1], c[2] - op[2]};
-                const double rj[3] = {c[0] - oj[0], c[1] - oj[1], c[2] - oj[2]};
-                double vi[3], vj[3];
-                cross3(ap, ri, vi);
-                cross3(aj, rj, vj);
-                const double Ia[3] = {I[0] * ap[0] + I[1] * ap[1] + I[2] * ap[2],
-                                      I[3] * ap[0] + I[4] * ap[1] + I[5] * ap[2],
-                                      I[6] * ap[0] + I[7] * ap[1] + I[8] * ap[2]};
-                m += ml * dot3(vi, vj) + dot3(aj, Ia);
-            }
-            pl.Ah[PD_GMAX * p + k] = m + (j == p ? cdiag : 0.0);
-            mom += m * pl.nuh[j];
+            const double m = pl.Ah[PD_GMAX * p + k];
+            mom += m * pl.nuh[g0 + k];
+            pl.Ah[PD_GMAX * p + k] = m + (g0 + k == p ? cdiag : 0.0);
         }
         pl.pm[p] = mom + dt * (double)Q.kp * ((double)u[T.jat(p)] - q_lane);
     }
@@ -307,81 +357,121 @@ __device__ __forceinline__ void pd_twists(int D, const float *x, const PdLds &pl
 }
 
 // Orders the contacts by (link, lane): pos = this contact's row; ends (bit r)
-// marks the rows that close a run of rows with one link, and linkrow the
-// first row of each link's run (-1: no contact on the link).
+// marks the rows that close a run of rows with one link, and linkrun the run
+// of each link (-1: no contact on the link).
 __device__ __forceinline__ void pd_order_contacts(const StepState<double> &st, const PdLds &pl, int &pos,
                                                   uint64_t &ends)
 {
-    const int lane = lane_id(), C = st.C;
+    const int lane = lane_here(), C = st.C;
     const int lk = st.act ? st.l : 0x7fffffff;
     int ps = 0;
     for (int c = 0; c < C; ++c) {
         const int o = __builtin_amdgcn_readlane(lk, c);
         ps += (o < lk || (o == lk && c < lane)) ? 1 : 0;
     }
-    pos = ps;
-    pl.linkrow[lane] = -1;
-    if (st.act) pl.rowlink[ps] = lk;
+    pos = st.act ? ps : lane;
+    int *rowlink = reinterpret_cast<int *>(pl.rows);   // [64]
+    pl.linkrun[lane] = -1;
+    if (st.act) rowlink[ps] = lk;
     wave_sync();
-    const bool start = lane < C && (lane == 0 || pl.rowlink[lane - 1] != pl.rowlink[lane]);
-    const bool end = lane < C && (lane == C - 1 || pl.rowlink[lane + 1] != pl.rowlink[lane]);
-    if (start) pl.linkrow[pl.rowlink[lane]] = lane;
+    const bool end = lane < C && (lane == C - 1 || rowlink[lane + 1] != rowlink[lane]);
     ends = __ballot(end);
+    if (end) pl.linkrun[rowlink[lane]] = mask_rank(ends);
     wave_sync();
 }
 
+// the runs whose links joint p moves
+__device__ __forceinline__ uint64_t pd_joint_runs(const PdTab &T, const PdLds &pl, int p)
+{
+    uint64_t r = 0;
+    for (uint64_t sb = T.sub(p); sb; sb &= sb - 1) {
+        const int k = pl.linkrun[__builtin_ctzll(sb)];
+        if (k >= 0) r |= 1ull << k;
+    }
+    return r;
+}
+
+// Task t < PD_GMAX D of the hand-hand blocks, entry (p, p's group's first + k)
+// with p = t / PD_GMAX, k = t % PD_GMAX: bits 0-7 the other joint's position,
+// bit 8 the pair moves a common link, bit 9 it is above the other (its links
+// include the other's); -1 past the group.
+__device__ __forceinline__ int pd_hand_task(const PdTab &T, int D, int t)
+{
+    const int p = t / PD_GMAX, k = t - PD_GMAX * p;
+    if (p >= D || k >= T.gn(p)) return -1;
+    const int j = T.gs(p) + k;
+    const uint64_t sj = T.sub(j), in = T.sub(p) & sj;
+    return j | (in != 0 ? 256 : 0) | (in == sj ? 512 : 0);
+}
+
+__device__ __forceinline__ void pd_lane_tables(const PdConsts &Q, const PdTab &T, const StepState<double> &st, int L,
+                                               int D, const PdLds &pl, PdLane &w)
+{
+    const int lane = lane_here();
+    w.chain = ~0ull;
+    if (st.act && st.l < L) {
+        w.chain = 0;
+#pragma unroll
+        for (int i = 0; i < PD_CHAIN; ++i) w.chain |= (uint64_t)(uint8_t)T.chain(st.l, i) << (8 * i);
+    }
+    const int g = lane / 7;
+    w.g0 = w.n = 0;
+    if (g < Q.groups) {
+        w.g0 = T.gfirst(g);
+        w.n = T.gfirst(g + 1) - w.g0;
+    }
+    w.x0 = pd_hand_task(T, D, lane);
+    w.x1 = pd_hand_task(T, D, lane + WAVE);
+    w.r0 = lane < 6 * D ? pd_joint_runs(T, pl, lane / 6) : 0;
+    w.r1 = lane + WAVE < 6 * D ? pd_joint_runs(T, pl, (lane + WAVE) / 6) : 0;
+}
+
 // Sums of N values per contact over each run of rows (one link) and over all
-// contacts: an active lane writes its values as row `pos` (the contacts are
-// lanes 0 .. C-1) and lanes C .. C16-1 zero rows C .. C16-1 (C16 = C rounded
-// up to 16), so that lanes e < N then read the rows sixteen at a time with
-// no bounds test and add them in row order (the zeros after the last run
-// change nothing), each run's sum overwriting its first row (a lane only
-// rewrites its own column of a row it has read) and the total landing in
-// tot[e].  The runs' ends (bit r of ends, r < C) are wave-uniform, so the
-// scan branches on them in scalar code.  buf: 16-byte aligned rows of
-// RedStride<double> doubles, at least C16 of them.
+// contacts, PD_ROWS rows at a time: the lanes whose row (pos; a lane past the
+// contacts has its own index) is among them write their values, then lanes
+// e < N read the rows with no bounds test and add them in row order (what
+// rows past the last run hold is added to nothing), each run's sum going to
+// its row of pl.sums and the total to pl.tot[e] after the last pass.  The
+// runs' ends (bit r of ends, r < C) are wave-uniform, so the scan branches on
+// them in scalar code.
 template <int N>
-__device__ __forceinline__ void pd_segsum(const double (&v)[N], bool act, int pos, int C, uint64_t ends,
-                                          double *buf, double *tot)
+__device__ __forceinline__ void pd_segsum(const double (&v)[N], int pos, int C, uint64_t ends, const PdLds &pl)
 {
     constexpr int RS = RedStride<double>::value;
-    static_assert(N <= RS, "row too long");
+    static_assert(N <= PD_SUM && N % 2 == 0, "rows of 16-byte words");
     const int lane = lane_id();
-    const int C16 = (C + 15) & ~15;
-    if (act) {
-        double *row = buf + pos * RS;
+    double t = 0.0, a = 0.0;
+    double *sum = pl.sums + lane;
+#pragma unroll 1
+    for (int r0 = 0; r0 < C; r0 += PD_ROWS) {
+        if (pos / PD_ROWS == r0 / PD_ROWS) {
+            double *row = pl.rows + (pos - r0) * RS;
 #pragma unroll
-        for (int j = 0; j + 2 <= N; j += 2) store16<double>(row + j, v + j);
-        if (N % 2) row[N - 1] = v[N - 1];
-    } else if (lane >= C && lane < C16) {
-        double *row = buf + lane * RS;
-        const double z[2] = {0.0, 0.0};
+            for (int j = 0; j < N; j += 2) store16<double>(row + j, v + j);
+        }
+        wave_sync();
+        if (lane < N) {
+            const uint32_t e16 = (uint32_t)(ends >> r0);
 #pragma unroll
-        for (int j = 0; j + 2 <= N; j += 2) store16<double>(row + j, z);
-        if (N % 2) row[N - 1] = 0.0;
-    }
-    wave_sync();
-    if (lane < N) {
-        double t = 0.0, a = 0.0;
-        int start = 0;
-        for (int r0 = 0; r0 < C; r0 += 16) {
-            double x[16];
+            for (int k0 = 0; k0 < PD_ROWS; k0 += 8) {
+                double x[8];
 #pragma unroll
-            for (int k = 0; k < 16; ++k) x[k] = buf[(r0 + k) * RS + lane];
+                for (int k = 0; k < 8; ++k) x[k] = pl.rows[(k0 + k) * RS + lane];
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int r = r0 + k;
-                a += x[k];
-                if ((ends >> r) & 1ull) {
-                    buf[start * RS + lane] = a;
-                    t += a;
-                    a = 0.0;
-                    start = r + 1;
+                for (int k = 0; k < 8; ++k) {
+                    a += x[k];
+                    if ((e16 >> (k0 + k)) & 1u) {
+                        *sum = a;
+                        sum += PD_SUM;
+                        t += a;
+                        a = 0.0;
+                    }
                 }
             }
         }
-        tot[lane] = t;
+        wave_sync();
     }
+    if (lane < N) pl.tot[lane] = t;
     wave_sync();
 }
 
@@ -389,15 +479,20 @@ __device__ __forceinline__ void pd_segsum(const double (&v)[N], bool act, int po
 // b's entry at position p is B1[p ld1 + c] for c < n1 and B2[p] for c == n1
 // (when B2 is given); y goes to Y[p ldy + c].  Gaussian elimination with
 // partial pivoting on the block padded to G (the batch's largest group,
-// at most PD_GMAX; rows of X at stride PD_GMAX) with the identity.
+// at most PD_GMAX; rows of X at stride PD_GMAX) with the identity.  With
+// seven right-hand sides w knows the first 64 tasks' groups.
 template <int G>
-__device__ __forceinline__ void pd_group_solve(const PdTab &T, int groups, const double *X, const double *B1, int ld1,
-                                               int n1, const double *B2, double *Y, int ldy)
+__device__ __forceinline__ void pd_group_solve(const PdTab &T, const PdLane &w, int groups, const double *X,
+                                               const double *B1, int ld1, int n1, const double *B2, double *Y, int ldy)
 {
     const int ncol = n1 + (B2 ? 1 : 0);
     for (int t = lane_id(); t < groups * ncol; t += WAVE) {
         const int g = t / ncol, c = t - g * ncol;
-        const int g0 = T.gfirst(g), n = T.gfirst(g + 1) - g0;
+        int g0 = w.g0, n = w.n;
+        if (ncol != 7 || t >= WAVE) {
+            g0 = T.gfirst(g);
+            n = T.gfirst(g + 1) - g0;
+        }
         double a[G][G], y[G];
 #pragma unroll
         for (int i = 0; i < G; ++i) {
@@ -443,20 +538,20 @@ __device__ __forceinline__ void pd_group_solve(const PdTab &T, int groups, const
     }
 }
 
-// twist of link l (l == L: the table, none) under joint rates w: the sum of
-// s_p w_p over the joints moving it
-__device__ __forceinline__ void pd_link_twist(const PdTab &T, int l, int L, const double *S, const double *w,
-                                              double *tw)
+// twist of this lane's contact's link under joint rates w: the sum of s_p w_p
+// over the joints moving it, positions in chain (PdLane)
+__device__ __forceinline__ void pd_link_twist(uint64_t chain, const double *S, const double *w, double *tw)
 {
 #pragma unroll
     for (int k = 0; k < 6; ++k) tw[k] = 0.0;
-    if (l < 0 || l >= L) return;
-    for (int i = 0; i < PD_CHAIN; ++i) {
-        const int p = T.chain(l, i);
-        if (p < 0) break;
-        const double wp = w[p];
+#pragma unroll 1
+    for (; __any((uint8_t)chain != 0xff); chain = chain >> 8 | 0xffull << 56) {
+        const int p = (uint8_t)chain;
+        if (p != 0xff) {
+            const double wp = w[p];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) tw[k] += S[6 * p + k] * wp;
+            for (int k = 0; k < 6; ++k) tw[k] += S[6 * p + k] * wp;
+        }
     }
 }
 
@@ -465,11 +560,10 @@ __device__ __forceinline__ void pd_link_twist(const PdTab &T, int l, int L, cons
 // about x on the links p moves), f the impulse on the object.  To pl.nuh.
 template <int G>
 __device__ __forceinline__ void pd_hand_rates(const Consts &P, const PdConsts &Q, const PdTab &T,
-                                              const StepState<double> &st, int pos, uint64_t ends, double *red,
+                                              const StepState<double> &st, const PdLane &lw, int pos, uint64_t ends,
                                               const PdLds &pl)
 {
-    constexpr int RS = RedStride<double>::value;
-    const int lane = lane_id(), D = P.D;
+    const int lane = lane_here(), D = P.D;
     double w6[6] = {0, 0, 0, 0, 0, 0};
     if (st.act) {
         const double *F = st.F, *r = st.r;
@@ -480,22 +574,19 @@ __device__ __forceinline__ void pd_hand_rates(const Consts &P, const PdConsts &Q
         w6[0] = f[0]; w6[1] = f[1]; w6[2] = f[2];
         w6[3] = t[0]; w6[4] = t[1]; w6[5] = t[2];
     }
-    pd_segsum<6>(w6, st.act, pos, st.C, ends, red, pl.tot);
+    pd_segsum<6>(w6, pos, st.C, ends, pl);
     if (lane < D) {
         const double *sp = pl.S + 6 * lane;
         double tau = 0.0;
-        for (uint64_t sb = T.sub(lane); sb; sb &= sb - 1) {
-            const int r0 = pl.linkrow[__builtin_ctzll(sb)];
-            if (r0 >= 0) {
-                const double *row = red + r0 * RS;
+        for (uint64_t rn = pd_joint_runs(T, pl, lane); rn; rn &= rn - 1) {
+            const double *row = pl.sums + __builtin_ctzll(rn) * PD_SUM;
 #pragma unroll
-                for (int k = 0; k < 6; ++k) tau -= sp[k] * row[k];
-            }
+            for (int k = 0; k < 6; ++k) tau -= sp[k] * row[k];
         }
         pl.zh[lane] = pl.pm[lane] + tau;
     }
     wave_sync();
-    pd_group_solve<G>(T, Q.groups, pl.Ah, pl.zh, 1, 1, nullptr, pl.nuh, 1);
+    pd_group_solve<G>(T, lw, Q.groups, pl.Ah, pl.zh, 1, 1, nullptr, pl.nuh, 1);
     wave_sync();
 }
 
@@ -504,13 +595,12 @@ __device__ __forceinline__ void pd_hand_rates(const Consts &P, const PdConsts &Q
 // pl.nuh (joint rates) for the final impulses.
 template <int G>
 __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q, const PdTab &T,
-                                              StepState<double> &st, float mu_f, const float *inv_in, double *red,
-                                              const PdLds &pl, int pos, uint64_t ends)
+                                              StepState<double> &st, float mu_f, const float *inv_in,
+                                              const PdLds &pl, const PdLane &lw, int pos, uint64_t ends)
 {
     using SR = double;
-    constexpr int RS = RedStride<double>::value;
     const SR eps = P.compliance, kap = P.kappa, del = P.fb_delta, mu = mu_f;
-    const int lane = lane_id(), L = P.L, D = P.D;
+    const int lane = lane_id(), D = P.D;
     BodyMass<SR> Mb;
     body_mass<SR>(st.m, st.Iinv, inv_in, Mb);
     const bool act = st.act;
@@ -520,19 +610,24 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
     body_dv(st, r, nu);
     nu[0] += st.vs[0]; nu[1] += st.vs[1]; nu[2] += st.vs[2];
     nu[3] += st.ws[0]; nu[4] += st.ws[1]; nu[5] += st.ws[2];
-    pd_hand_rates<G>(P, Q, T, st, pos, ends, red, pl);
+    pd_hand_rates<G>(P, Q, T, st, lw, pos, ends, pl);
     st.psi_end = st.C > 0 && P.newton_iters == 0 ? SR(-1) : SR(0);
     if (st.C > 0) {
         SR u[3];
         {
             SR tw[6], ne[6];
-            pd_link_twist(T, st.l, L, pl.S, pl.nuh, tw);
+            pd_link_twist(lw.chain, pl.S, pl.nuh, tw);
 #pragma unroll
             for (int k = 0; k < 6; ++k) ne[k] = nu[k] - tw[k];
             rel_velocity(st, ne, r, eps, u);
         }
         FBOut<SR> fo;
         fb_value(mu, kap, del, r, u, fo);
+        // the merit at the current impulses, that of the line search's
+        // accepted trial
+        SR psi = wave_sum1(act ? SR(0.5) * (fo.phi[0] * fo.phi[0] + fo.phi[1] * fo.phi[1] + fo.phi[2] * fo.phi[2])
+                               : SR(0), st.span);
+        const SR mass = body_mass_entry(Mb);
         for (int it = 0; it < P.newton_iters; ++it) {
             SR JX[9], JY[9];
             fb_jacobian(mu, kap, u, fo, JX, JY);
@@ -560,30 +655,25 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
                     Qw[3 * i + j] = F[i] * QF[j] + F[3 + i] * QF[3 + j] + F[6 + i] * QF[6 + j];
             const SR gw[3] = {F[0] * g[0] + F[3] * g[1] + F[6] * g[2], F[1] * g[0] + F[4] * g[1] + F[7] * g[2],
                               F[2] * g[0] + F[5] * g[1] + F[8] * g[2]};
-            SR acc[43];
+            SR acc[PD_SUM];
             schur_contribution(Qw, gw, rho, acc);
-            acc[42] = SR(0.5) * (fo.phi[0] * fo.phi[0] + fo.phi[1] * fo.phi[1] + fo.phi[2] * fo.phi[2]);
             // 1. per-link and total sums
-            pd_segsum<43>(acc, act, pos, st.C, ends, red, pl.tot);
-            const SR psi = pl.tot[42];
+            pd_segsum<PD_SUM>(acc, pos, st.C, ends, pl);
             // 2. object-hand blocks
-            for (int t = lane; t < 6 * D; t += WAVE) {
+            for (int t = lane, i = 0; t < 6 * D; t += WAVE, ++i) {
                 const int p = t / 6, k = t - 6 * (t / 6);
                 const SR *sp = pl.S + 6 * p;
                 SR aoh = 0, aho = 0, bh = 0;
-                for (uint64_t sb = T.sub(p); sb; sb &= sb - 1) {
-                    const int r0 = pl.linkrow[__builtin_ctzll(sb)];
-                    if (r0 >= 0) {
-                        const SR *K = red + r0 * RS;
+                for (uint64_t rn = i == 0 ? lw.r0 : (i == 1 ? lw.r1 : pd_joint_runs(T, pl, p)); rn; rn &= rn - 1) {
+                    const SR *K = pl.sums + __builtin_ctzll(rn) * PD_SUM;
 #pragma unroll
-                        for (int m = 0; m < 6; ++m) {
-                            aoh -= K[6 * k + m] * sp[m];
-                            aho -= sp[m] * K[6 * m + k];
-                        }
-                        if (k == 0) {
+                    for (int m = 0; m < 6; ++m) {
+                        aoh -= K[6 * k + m] * sp[m];
+                        aho -= sp[m] * K[6 * m + k];
+                    }
+                    if (k == 0) {
 #pragma unroll
-                            for (int m = 0; m < 6; ++m) bh -= sp[m] * K[36 + m];
-                        }
+                        for (int m = 0; m < 6; ++m) bh -= sp[m] * K[36 + m];
                     }
                 }
                 pl.Aoh[6 * p + k] = aoh;
@@ -591,35 +681,46 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
                 if (k == 0) pl.bh[p] = bh;
             }
             wave_sync();
-            for (int t = lane; t < PD_GMAX * D; t += WAVE) {
-                const int p = t / PD_GMAX, k = t - PD_GMAX * (t / PD_GMAX);
-                if (k < T.gn(p)) {
-                    const int j = T.gs(p) + k;
-                    const uint64_t si = T.sub(p), sj = T.sub(j), in = si & sj;
+            for (int t = lane, i = 0; t < PD_GMAX * D; t += WAVE, ++i) {
+                const int task = i == 0 ? lw.x0 : (i == 1 ? lw.x1 : pd_hand_task(T, D, t));
+                if (task >= 0) {
+                    const int p = t / PD_GMAX, j = task & 255;
                     SR h = 0;
-                    if (in != 0) {
-                        const SR *a = in == sj ? pl.S + 6 * p : pl.Aho + 6 * p;
-                        const SR *b = in == sj ? pl.Aoh + 6 * j : pl.S + 6 * j;
+                    if (task & 256) {
+                        const SR *a = task & 512 ? pl.S + 6 * p : pl.Aho + 6 * p;
+                        const SR *b = task & 512 ? pl.Aoh + 6 * j : pl.S + 6 * j;
 #pragma unroll
                         for (int m = 0; m < 6; ++m) h -= a[m] * b[m];
                     }
-                    pl.X[PD_GMAX * p + k] = pl.Ah[PD_GMAX * p + k] + h;
+                    pl.X[t] = pl.Ah[t] + h;
                 }
             }
             wave_sync();
             // 3. Y = X^-1 [A_ho | b_h] per group
-            pd_group_solve<G>(T, Q.groups, pl.X, pl.Aho, 6, 6, pl.bh, pl.Y, PD_YS);
+            pd_group_solve<G>(T, lw, Q.groups, pl.X, pl.Aho, 6, 6, pl.bh, pl.Y, PD_YS);
             wave_sync();
             // 4. the object's reduced 6x6 system and its solve
             if (lane < 42) {
                 SR s = pl.tot[lane];
                 const int rr = lane < 36 ? lane / 6 : lane - 36, cc = lane < 36 ? lane - 6 * (lane / 6) : 6;
-                for (int p = 0; p < D; ++p) s -= pl.Aoh[6 * p + rr] * pl.Y[PD_YS * p + cc];
-                pl.acc[lane] = s;
+                // in joint order, eight joints' reads in flight
+                for (int p0 = 0; p0 < D; p0 += 8) {
+                    SR x[8], y[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const int p = min(p0 + k, D - 1);
+                        x[k] = pl.Aoh[6 * p + rr];
+                        y[k] = pl.Y[PD_YS * p + cc];
+                    }
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        if (p0 + k < D) s -= x[k] * y[k];
+                }
+                pl.acc[lane] = s + mass;
             }
             wave_sync();
             SR z[6];
-            schur_solve(pl.acc, Mb, z);
+            schur_solve<SR, true>(pl.acc, Mb, z);
             if (lane < D) {
                 SR zh = -pl.Y[PD_YS * lane + 6];
 #pragma unroll
@@ -631,7 +732,7 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
             SR dz[6];
             {
                 SR tw[6];
-                pd_link_twist(T, st.l, L, pl.S, pl.zh, tw);
+                pd_link_twist(lw.chain, pl.S, pl.zh, tw);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) dz[k] = z[k] - tw[k];
             }
@@ -672,13 +773,14 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
                 u[i] = ut[i];
             }
             fo = ft;
+            psi = st.psi_end;
         }
     }
     // fresh sums for the final impulses
     body_dv(st, r, st.nu);
     st.nu[0] += st.vs[0]; st.nu[1] += st.vs[1]; st.nu[2] += st.vs[2];
     st.nu[3] += st.ws[0]; st.nu[4] += st.ws[1]; st.nu[5] += st.ws[2];
-    pd_hand_rates<G>(P, Q, T, st, pos, ends, red, pl);
+    pd_hand_rates<G>(P, Q, T, st, lw, pos, ends, pl);
 }
 
 // The joint state of a step staged by position (lane p: the joint at
@@ -716,7 +818,9 @@ __device__ __forceinline__ void pd_step(const Consts &P, const PdConsts &Q, cons
     int pos;
     uint64_t ends;
     pd_order_contacts(sst, pl, pos, ends);
-    step_solve_pd<G>(P, Q, T, sst, B.mu, inv, reinterpret_cast<double *>(lds.cand_d), pl, pos, ends);
+    PdLane lw;
+    pd_lane_tables(Q, T, sst, P.L, P.D, pl, lw);
+    step_solve_pd<G>(P, Q, T, sst, B.mu, inv, pl, lw, pos, ends);
     step_finish<double>(P, sst, inv, B, wkey, wr, link, imp);
 }
 
