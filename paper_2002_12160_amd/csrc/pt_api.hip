@@ -331,9 +331,19 @@ pt_status build_pd_table(const pt_batch_desc *d, std::vector<int32_t> &tab, int 
     }
     for (int l = 0; l < L; ++l) {
         tab[6 * D + l] = depth[l];
-        for (size_t i = 0; i < chain[l].size(); ++i) tab[6 * D + L + l * pt::PD_CHAIN + i] = pos[chain[l][i]];
+        uint64_t at = ~0ull;
+        for (size_t i = 0; i < chain[l].size(); ++i)
+            at = (at & ~(0xffull << (8 * i))) | (uint64_t)pos[chain[l][i]] << (8 * i);
+        tab[6 * D + L + 2 * l] = (int32_t)(uint32_t)(at & 0xffffffffu);
+        tab[6 * D + L + 2 * l + 1] = (int32_t)(uint32_t)(at >> 32);
     }
-    for (int g = 0; g <= groups; ++g) tab[6 * D + L + L * pt::PD_CHAIN + g] = gfirst[g];
+    for (int p = 0; p < D; ++p)
+        for (int k = 0; k < gn[p]; ++k) {
+            const int j = gs[p] + k;
+            const uint64_t in = sub[p] & sub[j];
+            tab[6 * D + 3 * L + p * pt::PD_GMAX + k] = j | (in != 0 ? 256 : 0) | (in == sub[j] ? 512 : 0);
+        }
+    for (int g = 0; g <= groups; ++g) tab[6 * D + 3 * L + pt::PD_GMAX * D + g] = gfirst[g];
     return PT_OK;
 }
 

@@ -22,7 +22,7 @@ namespace pt {
 // G: the batch's largest joint group, rounded up to 4 or PD_GMAX (the size
 // of the group eliminations)
 template <bool SDF, int G>
-__global__ __launch_bounds__(WAVE) void k_step_pd(Consts P, PdConsts Q, Tables tb, PdTab T,
+__global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2))) void k_step_pd(Consts P, PdConsts Q, Tables tb, PdTab T,
                                                   const float *__restrict__ u, float *__restrict__ state,
                                                   float *__restrict__ params, float *__restrict__ warm,
                                                   float *__restrict__ hstate, float *__restrict__ contacts,

@@ -72,13 +72,22 @@ struct PdTab {
         return (uint64_t)(uint32_t)t[4 * D + p] | ((uint64_t)(uint32_t)t[5 * D + p] << 32);
     }
     __device__ int depth(int l) const { return t[6 * D + l]; }
-    __device__ int chain(int l, int i) const { return t[6 * D + L + l * PD_CHAIN + i]; }   // -1 padded
-    __device__ int gfirst(int g) const { return t[6 * D + L + L * PD_CHAIN + g]; }        // [groups + 1]
+    // hand-hand block entry t < PD_GMAX D, of position p = t / PD_GMAX and its
+    // group's k-th, k = t % PD_GMAX: bits 0-7 the k-th's position, bit 8 the
+    // two move a common link, bit 9 p is above it (moves all its links); -1
+    // past the group
+    __device__ int hand_task(int i) const { return t[6 * D + L + 2 * L + i]; }
+    __device__ uint64_t chain(int l) const                               // positions moving link l, a byte each
+    {                                                                    // from the lowest, 0xff: no more
+        const int i = 6 * D + L + 2 * l;
+        return (uint64_t)(uint32_t)t[i] | ((uint64_t)(uint32_t)t[i + 1] << 32);
+    }
+    __device__ int gfirst(int g) const { return t[6 * D + 3 * L + PD_GMAX * D + g]; }     // [groups + 1]
 };
 
 __host__ __device__ constexpr size_t pd_tab_ints(int L, int D, int groups)
 {
-    return (size_t)6 * D + L + (size_t)L * PD_CHAIN + groups + 1;
+    return (size_t)6 * D + 3 * (size_t)L + (size_t)PD_GMAX * D + groups + 1;
 }
 
 // The contact sums go through LDS PD_ROWS contacts at a time, in the
@@ -180,7 +189,7 @@ struct PdLane {
     uint64_t chain;   // positions of the joints moving this lane's contact, a byte each from the
                       // lowest (0xff: no more)
     int g0, n;        // this lane's group in the group solves (lane / 7), n = 0: none
-    int x0, x1;       // its hand-hand tasks (0 and 1), see pd_hand_task
+    int x0, x1;       // its hand-hand tasks (PdTab::hand_task)
     uint64_t r0, r1;  // the runs that the joints of its object-hand tasks (0 and 1) move
 };
 
@@ -193,9 +202,24 @@ struct PdLane {
 __device__ __forceinline__ void pd_fk(const Consts &P, const PdConsts &Q, const PdTab &T,
                                       const float *__restrict__ hand, double *fk, const PdLds &pl, float *seg)
 {
-    const int L = P.L, lane = lane_id();
+    const int L = P.L, lane = lane_here();   // one lane per link
     double *tq = fk, *tb = fk + 4 * L, *com = fk + 7 * L, *Iw = fk + 10 * L;
-    // the transcendental part for all joints at once
+    // the link's record and its joints' positions, and the transcendental
+    // part of all joints at once, ahead of the walk down the tree
+    float h[HAND_STRIDE];
+    int depth = -1, pj[2] = {-1, -1};
+    if (lane < L) {
+        const float4 *h4 = reinterpret_cast<const float4 *>(hand + (size_t)lane * HAND_STRIDE);
+#pragma unroll
+        for (int i = 0; i < HAND_STRIDE / 4; ++i) {
+            const float4 v = h4[i];
+            h[4 * i] = v.x; h[4 * i + 1] = v.y; h[4 * i + 2] = v.z; h[4 * i + 3] = v.w;
+        }
+        depth = T.depth(lane);
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if ((int)h[1 + k] >= 0) pj[k] = T.pos((int)h[1 + k]);
+    }
     if (lane < P.D) {
         double sn, cs;
         sincos(0.5 * pl.zh[lane], &sn, &cs);
@@ -203,10 +227,9 @@ __device__ __forceinline__ void pd_fk(const Consts &P, const PdConsts &Q, const 
         pl.Aho[2 * lane + 1] = cs;
     }
     wave_sync();
+    double o[3] = {0, 0, 0}, b[3] = {0, 0, 0}, R[9];
     for (int d = 0; d <= Q.dmax; ++d) {
-        for (int l = lane; l < L; l += WAVE) {
-            if (T.depth(l) != d) continue;
-            const float *h = hand + (size_t)l * HAND_STRIDE;
+        if (depth == d) {
             const int parent = (int)h[0];
             double pq[4] = {1, 0, 0, 0}, pp[3] = {0, 0, 0};
             if (parent >= 0) {
@@ -218,16 +241,15 @@ __device__ __forceinline__ void pd_fk(const Consts &P, const PdConsts &Q, const 
             double Rp[9];
             quat_to_mat_d(pq, Rp);
             const double off[3] = {h[9], h[10], h[11]};
-            double o[3];
 #pragma unroll
             for (int i = 0; i < 3; ++i) o[i] = pp[i] + Rp[3 * i] * off[0] + Rp[3 * i + 1] * off[1] + Rp[3 * i + 2] * off[2];
             const double qo[4] = {h[12], h[13], h[14], h[15]};
             double qf[4];
             quat_mul_d(pq, qo, qf);
+#pragma unroll
             for (int k = 0; k < 2; ++k) {
-                const int j = (int)h[1 + k];
-                if (j < 0) continue;
-                const int p = T.pos(j);
+                const int p = pj[k];
+                if (p < 0) continue;
                 const double ax[3] = {h[3 + 3 * k], h[4 + 3 * k], h[5 + 3 * k]};
                 double Rf[9];
                 quat_to_mat_d(qf, Rf);
@@ -244,53 +266,43 @@ __device__ __forceinline__ void pd_fk(const Consts &P, const PdConsts &Q, const 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) qf[i] = t[i];
             }
-            double R[9];
             quat_to_mat_d(qf, R);
-            const double len = h[16], rad = h[17];
-            double b[3], c[3];
+            const double len = h[16];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                b[i] = o[i] + len * R[3 * i];
-                c[i] = o[i] + 0.5 * len * R[3 * i];
-            }
+            for (int i = 0; i < 3; ++i) b[i] = o[i] + len * R[3 * i];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) tq[4 * l + i] = qf[i];
+            for (int i = 0; i < 4; ++i) tq[4 * lane + i] = qf[i];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                tb[3 * l + i] = b[i];
-                com[3 * l + i] = c[i];
-            }
-            // solid cylinder about its centre: axial m r^2 / 2, transverse m (3 r^2 + len^2) / 12
-            const double ml = Q.link_mass;
-            const double Ib[3] = {0.5 * ml * rad * rad, ml * (3 * rad * rad + len * len) / 12.0,
-                                  ml * (3 * rad * rad + len * len) / 12.0};
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-                    Iw[9 * l + 3 * i + j] =
-                        R[3 * i] * Ib[0] * R[3 * j] + R[3 * i + 1] * Ib[1] * R[3 * j + 1] + R[3 * i + 2] * Ib[2] * R[3 * j + 2];
-            float *sg = seg + (size_t)l * SEG_STRIDE;
-            float a0[3], ab[3];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                a0[i] = (float)o[i];
-                ab[i] = (float)(b[i] - o[i]);
-            }
-            const float L2 = ab[0] * ab[0] + ab[1] * ab[1] + ab[2] * ab[2];
-            const float inv = sqrtf(L2) >= 1e-9f ? 1.f / L2 : 0.f;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                sg[i] = a0[i];
-                sg[4 + i] = ab[i];
-            }
-            sg[3] = h[17];
-            sg[7] = inv;
-#pragma unroll
-            for (int i = 8; i < 16; ++i) sg[i] = 0.f;
+            for (int i = 0; i < 3; ++i) tb[3 * lane + i] = b[i];
         }
         wave_sync();
     }
+    // what the links below do not wait for
+    if (lane < L) {
+        const double len = h[16], rad = h[17];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) com[3 * lane + i] = o[i] + 0.5 * len * R[3 * i];
+        // solid cylinder about its centre: axial m r^2 / 2, transverse m (3 r^2 + len^2) / 12
+        const double ml = Q.link_mass;
+        const double Ib[3] = {0.5 * ml * rad * rad, ml * (3 * rad * rad + len * len) / 12.0,
+                              ml * (3 * rad * rad + len * len) / 12.0};
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                Iw[9 * lane + 3 * i + j] =
+                    R[3 * i] * Ib[0] * R[3 * j] + R[3 * i + 1] * Ib[1] * R[3 * j + 1] + R[3 * i + 2] * Ib[2] * R[3 * j + 2];
+        float4 *sg = reinterpret_cast<float4 *>(seg + (size_t)lane * SEG_STRIDE);
+        float ab[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) ab[i] = (float)(b[i] - o[i]);
+        const float L2 = ab[0] * ab[0] + ab[1] * ab[1] + ab[2] * ab[2];
+        const float inv = sqrtf(L2) >= 1e-9f ? 1.f / L2 : 0.f;
+        sg[0] = make_float4((float)o[0], (float)o[1], (float)o[2], h[17]);
+        sg[1] = make_float4(ab[0], ab[1], ab[2], inv);
+        sg[2] = sg[3] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    wave_sync();
 }
 
 // The group blocks of A_h = M(q) + (dt kd + dt^2 kp) I, one lane per entry,
@@ -391,37 +403,19 @@ __device__ __forceinline__ uint64_t pd_joint_runs(const PdTab &T, const PdLds &p
     return r;
 }
 
-// Task t < PD_GMAX D of the hand-hand blocks, entry (p, p's group's first + k)
-// with p = t / PD_GMAX, k = t % PD_GMAX: bits 0-7 the other joint's position,
-// bit 8 the pair moves a common link, bit 9 it is above the other (its links
-// include the other's); -1 past the group.
-__device__ __forceinline__ int pd_hand_task(const PdTab &T, int D, int t)
-{
-    const int p = t / PD_GMAX, k = t - PD_GMAX * p;
-    if (p >= D || k >= T.gn(p)) return -1;
-    const int j = T.gs(p) + k;
-    const uint64_t sj = T.sub(j), in = T.sub(p) & sj;
-    return j | (in != 0 ? 256 : 0) | (in == sj ? 512 : 0);
-}
-
 __device__ __forceinline__ void pd_lane_tables(const PdConsts &Q, const PdTab &T, const StepState<double> &st, int L,
                                                int D, const PdLds &pl, PdLane &w)
 {
     const int lane = lane_here();
-    w.chain = ~0ull;
-    if (st.act && st.l < L) {
-        w.chain = 0;
-#pragma unroll
-        for (int i = 0; i < PD_CHAIN; ++i) w.chain |= (uint64_t)(uint8_t)T.chain(st.l, i) << (8 * i);
-    }
+    w.chain = st.act && st.l < L ? T.chain(st.l) : ~0ull;
     const int g = lane / 7;
     w.g0 = w.n = 0;
     if (g < Q.groups) {
         w.g0 = T.gfirst(g);
         w.n = T.gfirst(g + 1) - w.g0;
     }
-    w.x0 = pd_hand_task(T, D, lane);
-    w.x1 = pd_hand_task(T, D, lane + WAVE);
+    w.x0 = lane < PD_GMAX * D ? T.hand_task(lane) : -1;
+    w.x1 = lane + WAVE < PD_GMAX * D ? T.hand_task(lane + WAVE) : -1;
     w.r0 = lane < 6 * D ? pd_joint_runs(T, pl, lane / 6) : 0;
     w.r1 = lane + WAVE < 6 * D ? pd_joint_runs(T, pl, (lane + WAVE) / 6) : 0;
 }
@@ -439,7 +433,7 @@ __device__ __forceinline__ void pd_segsum(const double (&v)[N], int pos, int C, 
 {
     constexpr int RS = RedStride<double>::value;
     static_assert(N <= PD_SUM && N % 2 == 0, "rows of 16-byte words");
-    const int lane = lane_id();
+    const int lane = lane_here();
     double t = 0.0, a = 0.0;
     double *sum = pl.sums + lane;
 #pragma unroll 1
@@ -486,14 +480,14 @@ __device__ __forceinline__ void pd_group_solve(const PdTab &T, const PdLane &w, 
                                                const double *B1, int ld1, int n1, const double *B2, double *Y, int ldy)
 {
     const int ncol = n1 + (B2 ? 1 : 0);
-    for (int t = lane_id(); t < groups * ncol; t += WAVE) {
+    for (int t = lane_here(); t < groups * ncol; t += WAVE) {
         const int g = t / ncol, c = t - g * ncol;
         int g0 = w.g0, n = w.n;
         if (ncol != 7 || t >= WAVE) {
             g0 = T.gfirst(g);
             n = T.gfirst(g + 1) - g0;
         }
-        double a[G][G], y[G];
+        double a[G][G], y[G], inv[G];
 #pragma unroll
         for (int i = 0; i < G; ++i) {
 #pragma unroll
@@ -516,10 +510,10 @@ __device__ __forceinline__ void pd_group_solve(const PdTab &T, const PdLane &w, 
                 y[k] = sw ? yi : yk;
                 y[i] = sw ? yk : yi;
             }
-            const double inv = 1.0 / a[k][k];
+            inv[k] = 1.0 / a[k][k];
 #pragma unroll
             for (int i = k + 1; i < G; ++i) {
-                const double f = a[i][k] * inv;
+                const double f = a[i][k] * inv[k];
 #pragma unroll
                 for (int m = k + 1; m < G; ++m) a[i][m] -= f * a[k][m];
                 y[i] -= f * y[k];
@@ -530,7 +524,12 @@ __device__ __forceinline__ void pd_group_solve(const PdTab &T, const PdLane &w, 
             double s = y[k];
 #pragma unroll
             for (int m = k + 1; m < G; ++m) s -= a[k][m] * y[m];
-            y[k] = s / a[k][k];
+            // s / a[k][k], correctly rounded: with the correctly rounded
+            // reciprocal one exact remainder (FMA) and one correction of the
+            // product give the quotient (Markstein), three operations on the
+            // chain instead of a division's ten
+            const double q = s * inv[k];
+            y[k] = fma(fma(-a[k][k], q, s), inv[k], q);
         }
 #pragma unroll
         for (int i = 0; i < G; ++i)
@@ -540,17 +539,36 @@ __device__ __forceinline__ void pd_group_solve(const PdTab &T, const PdLane &w, 
 
 // twist of this lane's contact's link under joint rates w: the sum of s_p w_p
 // over the joints moving it, positions in chain (PdLane)
+template <int G>
 __device__ __forceinline__ void pd_link_twist(uint64_t chain, const double *S, const double *w, double *tw)
 {
 #pragma unroll
     for (int k = 0; k < 6; ++k) tw[k] = 0.0;
-#pragma unroll 1
-    for (; __any((uint8_t)chain != 0xff); chain = chain >> 8 | 0xffull << 56) {
-        const int p = (uint8_t)chain;
-        if (p != 0xff) {
-            const double wp = w[p];
+    // a link's joints lie in one group: at most G of them, the first four's
+    // values read ahead of the sum
+    double wp[4], s[4][6];
 #pragma unroll
-            for (int k = 0; k < 6; ++k) tw[k] += S[6 * p + k] * wp;
+    for (int i = 0; i < 4; ++i) {
+        const int p = (uint8_t)(chain >> (8 * i));
+        if (p != 0xff) {
+            wp[i] = w[p];
+#pragma unroll
+            for (int k = 0; k < 6; k += 2) load16<double>(S + 6 * p + k, s[i] + k);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if ((uint8_t)(chain >> (8 * i)) != 0xff) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) tw[k] += s[i][k] * wp[i];
+        }
+#pragma unroll
+    for (int i = 4; i < G; ++i) {
+        const int p = (uint8_t)(chain >> (8 * i));
+        if (p != 0xff) {
+            const double wi = w[p];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) tw[k] += S[6 * p + k] * wi;
         }
     }
 }
@@ -590,6 +608,50 @@ __device__ __forceinline__ void pd_hand_rates(const Consts &P, const PdConsts &Q
     wave_sync();
 }
 
+// One task of the object-hand blocks: component k of joint p's column of A_oh
+// and row of A_ho (and, with k = 0, b_h) summed over the runs of contacts on
+// the links it moves, lowest link first.
+struct PdBlocks {
+    uint64_t runs;       // still to add
+    double sp[6], aoh, aho, bh;
+
+    __device__ __forceinline__ void start(const double *s, uint64_t r)
+    {
+        runs = r;
+        aoh = aho = bh = 0.0;
+#pragma unroll
+        for (int m = 0; m < 6; m += 2) load16<double>(s + m, sp + m);
+    }
+    // adds the next run; a task that is done reads the first one and keeps
+    // its sums (no divergent branch around the reads)
+    __device__ __forceinline__ void step(const double *sums, int k)
+    {
+        const bool on = runs != 0;
+        const double *K = sums + (on ? __builtin_ctzll(runs) * PD_SUM : 0);
+        double row[6], b[6], x = aoh, y = aho, z = bh;
+#pragma unroll
+        for (int m = 0; m < 6; m += 2) load16<double>(K + 6 * k + m, row + m);
+#pragma unroll
+        for (int m = 0; m < 6; m += 2) load16<double>(K + 36 + m, b + m);
+#pragma unroll
+        for (int m = 0; m < 6; ++m) {
+            x -= row[m] * sp[m];
+            y -= sp[m] * K[6 * m + k];
+            z -= sp[m] * b[m];
+        }
+        aoh = on ? x : aoh;
+        aho = on ? y : aho;
+        bh = on ? z : bh;
+        runs &= runs - 1;
+    }
+    __device__ __forceinline__ void store(const PdLds &pl, int p, int k) const
+    {
+        pl.Aoh[6 * p + k] = aoh;
+        pl.Aho[6 * p + k] = aho;
+        if (k == 0) pl.bh[p] = bh;
+    }
+};
+
 // The contact solve of a PD step (the kinematic path's Newton method over
 // the generalised velocity (v, w, qdot)); leaves st.r, st.nu (object) and
 // pl.nuh (joint rates) for the final impulses.
@@ -616,7 +678,7 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
         SR u[3];
         {
             SR tw[6], ne[6];
-            pd_link_twist(lw.chain, pl.S, pl.nuh, tw);
+            pd_link_twist<G>(lw.chain, pl.S, pl.nuh, tw);
 #pragma unroll
             for (int k = 0; k < 6; ++k) ne[k] = nu[k] - tw[k];
             rel_velocity(st, ne, r, eps, u);
@@ -659,30 +721,31 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
             schur_contribution(Qw, gw, rho, acc);
             // 1. per-link and total sums
             pd_segsum<PD_SUM>(acc, pos, st.C, ends, pl);
-            // 2. object-hand blocks
-            for (int t = lane, i = 0; t < 6 * D; t += WAVE, ++i) {
-                const int p = t / 6, k = t - 6 * (t / 6);
-                const SR *sp = pl.S + 6 * p;
-                SR aoh = 0, aho = 0, bh = 0;
-                for (uint64_t rn = i == 0 ? lw.r0 : (i == 1 ? lw.r1 : pd_joint_runs(T, pl, p)); rn; rn &= rn - 1) {
-                    const SR *K = pl.sums + __builtin_ctzll(rn) * PD_SUM;
-#pragma unroll
-                    for (int m = 0; m < 6; ++m) {
-                        aoh -= K[6 * k + m] * sp[m];
-                        aho -= sp[m] * K[6 * m + k];
-                    }
-                    if (k == 0) {
-#pragma unroll
-                        for (int m = 0; m < 6; ++m) bh -= sp[m] * K[36 + m];
-                    }
+            // 2. object-hand blocks, the lane's first two tasks side by side
+            {
+                const int lane = lane_here();
+                const int t1 = lane + WAVE, p0 = lane / 6, k0 = lane - 6 * p0, p1 = t1 / 6, k1 = t1 - 6 * p1;
+                PdBlocks x0, x1;
+                x0.start(pl.S + 6 * max(min(p0, D - 1), 0), lw.r0);
+                x1.start(pl.S + 6 * max(min(p1, D - 1), 0), lw.r1);
+#pragma unroll 1
+                while (__any((x0.runs | x1.runs) != 0)) {
+                    x0.step(pl.sums, k0);
+                    x1.step(pl.sums, k1);
                 }
-                pl.Aoh[6 * p + k] = aoh;
-                pl.Aho[6 * p + k] = aho;
-                if (k == 0) pl.bh[p] = bh;
+                if (lane < 6 * D) x0.store(pl, p0, k0);
+                if (t1 < 6 * D) x1.store(pl, p1, k1);
+#pragma unroll 1
+                for (int t = t1 + WAVE; t - lane < 6 * D; t += WAVE) {
+                    const int p = t / 6, k = t - 6 * p;
+                    x0.start(pl.S + 6 * min(p, D - 1), t < 6 * D ? pd_joint_runs(T, pl, p) : 0);
+                    while (__any(x0.runs != 0)) x0.step(pl.sums, k);
+                    if (t < 6 * D) x0.store(pl, p, k);
+                }
             }
             wave_sync();
-            for (int t = lane, i = 0; t < PD_GMAX * D; t += WAVE, ++i) {
-                const int task = i == 0 ? lw.x0 : (i == 1 ? lw.x1 : pd_hand_task(T, D, t));
+            for (int t = lane_here(), i = 0; t < PD_GMAX * D; t += WAVE, ++i) {
+                const int task = i == 0 ? lw.x0 : (i == 1 ? lw.x1 : T.hand_task(t));
                 if (task >= 0) {
                     const int p = t / PD_GMAX, j = task & 255;
                     SR h = 0;
@@ -700,7 +763,7 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
             pd_group_solve<G>(T, lw, Q.groups, pl.X, pl.Aho, 6, 6, pl.bh, pl.Y, PD_YS);
             wave_sync();
             // 4. the object's reduced 6x6 system and its solve
-            if (lane < 42) {
+            if (const int lane = lane_here(); lane < 42) {
                 SR s = pl.tot[lane];
                 const int rr = lane < 36 ? lane / 6 : lane - 36, cc = lane < 36 ? lane - 6 * (lane / 6) : 6;
                 // in joint order, eight joints' reads in flight
@@ -732,7 +795,7 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
             SR dz[6];
             {
                 SR tw[6];
-                pd_link_twist(lw.chain, pl.S, pl.zh, tw);
+                pd_link_twist<G>(lw.chain, pl.S, pl.zh, tw);
 #pragma unroll
                 for (int k = 0; k < 6; ++k) dz[k] = z[k] - tw[k];
             }
