@@ -492,8 +492,17 @@ __device__ __forceinline__ void pd_group_solve(const PdTab &T, const PdLane &w, 
         for (int i = 0; i < G; ++i) {
 #pragma unroll
             for (int k = 0; k < G; ++k)
-                a[i][k] = (i < n && k < n) ? X[PD_GMAX * (g0 + i) + k] : (i == k ? 1.0 : 0.0);
-            y[i] = i < n ? (c < n1 ? B1[(size_t)(g0 + i) * ld1 + c] : B2[g0 + i]) : 0.0;
+                a[i][k] = X[PD_GMAX * (g0 + min(i, n - 1)) + min(k, n - 1)];
+            const int at = g0 + min(i, n - 1);
+            y[i] = *(c < n1 ? B1 + (size_t)at * ld1 + c : B2 + at);
+        }
+        // the padding, after reads that no lane branches around
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+                if (i >= n || k >= n) a[i][k] = i == k ? 1.0 : 0.0;
+            if (i >= n) y[i] = 0.0;
         }
 #pragma unroll
         for (int k = 0; k < G; ++k) {
@@ -652,6 +661,19 @@ struct PdBlocks {
     }
 };
 
+// Entry t of X = A_h + the hand-hand block (task: PdTab::hand_task; a task
+// past the group reads entry 0 and its value is not used)
+__device__ __forceinline__ double pd_hand_entry(const PdLds &pl, int t, int task)
+{
+    const bool on = task >= 0, above = task & 512;
+    const int p = on ? t / PD_GMAX : 0, j = on ? task & 255 : 0;
+    const double *a = (above ? pl.S : pl.Aho) + 6 * p, *b = (above ? pl.Aoh : pl.S) + 6 * j;
+    double h = 0.0;
+#pragma unroll
+    for (int m = 0; m < 6; ++m) h -= a[m] * b[m];
+    return pl.Ah[on ? t : 0] + (on && (task & 256) ? h : 0.0);
+}
+
 // The contact solve of a PD step (the kinematic path's Newton method over
 // the generalised velocity (v, w, qdot)); leaves st.r, st.nu (object) and
 // pl.nuh (joint rates) for the final impulses.
@@ -744,18 +766,15 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
                 }
             }
             wave_sync();
-            for (int t = lane_here(), i = 0; t < PD_GMAX * D; t += WAVE, ++i) {
-                const int task = i == 0 ? lw.x0 : (i == 1 ? lw.x1 : T.hand_task(t));
-                if (task >= 0) {
-                    const int p = t / PD_GMAX, j = task & 255;
-                    SR h = 0;
-                    if (task & 256) {
-                        const SR *a = task & 512 ? pl.S + 6 * p : pl.Aho + 6 * p;
-                        const SR *b = task & 512 ? pl.Aoh + 6 * j : pl.S + 6 * j;
-#pragma unroll
-                        for (int m = 0; m < 6; ++m) h -= a[m] * b[m];
-                    }
-                    pl.X[t] = pl.Ah[t] + h;
+            {
+                const int lane = lane_here();
+                const SR h0 = pd_hand_entry(pl, lane, lw.x0), h1 = pd_hand_entry(pl, lane + WAVE, lw.x1);
+                if (lw.x0 >= 0) pl.X[lane] = h0;
+                if (lw.x1 >= 0) pl.X[lane + WAVE] = h1;
+                for (int t = lane + 2 * WAVE; t < PD_GMAX * D; t += WAVE) {
+                    const int task = T.hand_task(t);
+                    const SR h = pd_hand_entry(pl, t, task);
+                    if (task >= 0) pl.X[t] = h;
                 }
             }
             wave_sync();
@@ -766,19 +785,19 @@ __device__ __forceinline__ void step_solve_pd(const Consts &P, const PdConsts &Q
             if (const int lane = lane_here(); lane < 42) {
                 SR s = pl.tot[lane];
                 const int rr = lane < 36 ? lane / 6 : lane - 36, cc = lane < 36 ? lane - 6 * (lane / 6) : 6;
-                // in joint order, eight joints' reads in flight
-                for (int p0 = 0; p0 < D; p0 += 8) {
-                    SR x[8], y[8];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const int p = min(p0 + k, D - 1);
-                        x[k] = pl.Aoh[6 * p + rr];
-                        y[k] = pl.Y[PD_YS * p + cc];
-                    }
-#pragma unroll
-                    for (int k = 0; k < 8; ++k)
-                        if (p0 + k < D) s -= x[k] * y[k];
+                // in joint order, four joints' reads in flight ahead of their sum
+                const SR *x = pl.Aoh + rr, *y = pl.Y + cc;
+                int p = 0;
+                for (; p + 4 <= D; p += 4) {
+                    const SR x0 = x[6 * p], x1 = x[6 * p + 6], x2 = x[6 * p + 12], x3 = x[6 * p + 18];
+                    const SR *yp = y + PD_YS * p;
+                    const SR y0 = yp[0], y1 = yp[PD_YS], y2 = yp[2 * PD_YS], y3 = yp[3 * PD_YS];
+                    s -= x0 * y0;
+                    s -= x1 * y1;
+                    s -= x2 * y2;
+                    s -= x3 * y3;
                 }
+                for (; p < D; ++p) s -= x[6 * p] * y[PD_YS * p];
                 pl.acc[lane] = s + mass;
             }
             wave_sync();
