@@ -357,7 +357,7 @@ int max_wpb(const Consts &P) { return P.solve_fp64 ? 4 : 8; }
 // refinement buffers of n elites, carved from one allocation (every block a
 // multiple of 4 floats, so the warm caches stay 16-byte aligned)
 struct RefineBufs {
-    float *xi, *xi_try, *g, *cost, *cost_try, *rho, *end_state, *end_warm, *warm0;
+    float *xi, *xi_try, *g, *cost, *rho, *warm0;
     int32_t *flag;
 };
 
@@ -365,24 +365,20 @@ static size_t pad4(size_t x) { return (x + 3) / 4 * 4; }
 
 static size_t refine_floats(const Consts &P, int n)
 {
-    const size_t w = (size_t)n * P.C_max * 4;
-    return 3 * pad4((size_t)pt::XI_ROWS * n) + 4 * pad4(n) + pad4(13 * (size_t)n) + 2 * w;
+    return 3 * pad4((size_t)pt::XI_ROWS * n) + 3 * pad4(n) + (size_t)n * P.C_max * 4;
 }
 
 static RefineBufs refine_layout(float *base, const Consts &P, int n)
 {
     RefineBufs r;
-    const size_t x = pad4((size_t)pt::XI_ROWS * n), v = pad4(n), w = (size_t)n * P.C_max * 4;
+    const size_t x = pad4((size_t)pt::XI_ROWS * n), v = pad4(n);
     r.xi = base;
     r.xi_try = r.xi + x;
     r.g = r.xi_try + x;
     r.cost = r.g + x;
-    r.cost_try = r.cost + v;
-    r.rho = r.cost_try + v;
+    r.rho = r.cost + v;
     r.flag = reinterpret_cast<int32_t *>(r.rho + v);
-    r.end_state = r.rho + 2 * v;
-    r.end_warm = r.end_state + pad4(13 * (size_t)n);
-    r.warm0 = r.end_warm + w;
+    r.warm0 = r.rho + 2 * v;
     return r;
 }
 
@@ -998,6 +994,8 @@ pt_status pt_refine_elites(pt_batch b, const float *u_win, const float *obs_gt_w
             part[np++] = {i0, cnt, k == 0 ? st : b->side_stream[k - 1], b->d_ckpt + ckpt_floats(P, i0)};
             i0 += cnt;
         }
+        const pt::RefineTry next = {A, r.rho, r.xi_try};
+        const pt::RefineKeep keep = {r.cost, r.xi, r.rho, r.flag, b->state, b->params, b->warm, cost_sum};
         if (np > 1) {
             HIP_TRY(hipEventRecord(b->ev_fork, st));
             for (int k = 1; k < np; ++k) HIP_TRY(hipStreamWaitEvent(part[k].s, b->ev_fork, 0));
@@ -1008,24 +1006,21 @@ pt_status pt_refine_elites(pt_batch b, const float *u_win, const float *obs_gt_w
                 HIP_TRY(launch_window_fwd(P, tb, b->d_seg_grad, n, c.i0, c.count, b->d_elite, r.xi, r.warm0,
                                           obs_gt_win, r.cost, nullptr, nullptr, c.ckpt, c.s));
             HIP_TRY(launch_window_bwd(P, tb, b->d_seg_grad, n, c.i0, c.count, b->d_elite, r.xi, obs_gt_win,
-                                      from_window ? b->d_wckpt : c.ckpt, from_window, nullptr, r.g, c.s));
+                                      from_window ? b->d_wckpt : c.ckpt, from_window, nullptr, r.g, c.s, &next));
         }
         for (int it = 0; it < steps; ++it) {
-            // trial, its replay (checkpointed unless it is the last), keep or
-            // halve, then the gradient at the kept trials only
+            // the trial's replay (checkpointed unless it is the last), which
+            // keeps it or halves the step; then the gradient at the kept
+            // trials, and every elite's next trial from its gradient
             const bool last = it == steps - 1;
             for (int k = 0; k < np; ++k) {
                 const Part &c = part[k];
-                HIP_TRY(launch_refine_propose(n, c.i0, c.count, A, r.xi, r.g, r.rho, r.xi_try, c.s));
                 HIP_TRY(launch_window_fwd(P, tb, b->d_seg_grad, n, c.i0, c.count, b->d_elite, r.xi_try, r.warm0,
-                                          obs_gt_win, r.cost_try, r.end_state, r.end_warm, last ? nullptr : c.ckpt,
-                                          c.s));
-                HIP_TRY(launch_refine_accept(n, c.i0, c.count, P.K, P.C_max, b->d_elite, r.cost, r.cost_try, r.xi,
-                                             r.xi_try, r.rho, r.flag, r.end_state, r.end_warm, b->state, b->params,
-                                             b->warm, cost_sum, c.s));
+                                          obs_gt_win, nullptr, nullptr, nullptr, last ? nullptr : c.ckpt, c.s, nullptr,
+                                          &keep));
                 if (!last)
                     HIP_TRY(launch_window_bwd(P, tb, b->d_seg_grad, n, c.i0, c.count, b->d_elite, r.xi, obs_gt_win,
-                                              c.ckpt, false, r.flag, r.g, c.s));
+                                              c.ckpt, false, r.flag, r.g, c.s, &next));
             }
         }
         for (int k = 1; k < np; ++k) {

@@ -14,7 +14,12 @@
 //                     Output: the gradient of the window cost with respect
 //                     to the start (x, q, v, w, m, mu, f)
 //   (the elites come from the resampler's own ranking, k_rank)
-//   k_refine_*        gather / scaled gradient step / accept-or-halve
+//   k_refine_gather   the elites' window starts; the scaled gradient step is
+//                     the reverse sweep's last act and keep-or-halve the
+//                     forward sweep's (kernels of their own waited behind the
+//                     sweeps that fill the GPU: 130 us a gradient step)
+#include <algorithm>
+
 #include "pt_adjoint.hpp"
 #include "pt_internal.h"
 #include "pt_io.hpp"
@@ -42,7 +47,8 @@ __global__ __launch_bounds__(WAVE) void k_window_fwd(Consts P, Tables tb, const 
                                                      const float *__restrict__ warm0,
                                                      const float *__restrict__ obs_gt_win, float *__restrict__ cost_out,
                                                      float *__restrict__ end_state, float *__restrict__ end_warm,
-                                                     float *__restrict__ ckpt, float *__restrict__ resid_out)
+                                                     float *__restrict__ ckpt, float *__restrict__ resid_out,
+                                                     RefineKeep keep)
 {
     extern __shared__ __align__(16) char smem[];
     const int c = blockIdx.x;
@@ -52,7 +58,7 @@ __global__ __launch_bounds__(WAVE) void k_window_fwd(Consts P, Tables tb, const 
     const int e = env[i];
     if (e < 0 || e >= P.K) {
         // not a simulation of this batch
-        if (lane == 0) cost_out[i] = __int_as_float(0x7fc00000);
+        if (lane == 0 && cost_out) cost_out[i] = __int_as_float(0x7fc00000);
         return;
     }
     WaveLds lds = carve_lds(smem, 0, P.max_cand, 0);
@@ -102,6 +108,30 @@ __global__ __launch_bounds__(WAVE) void k_window_fwd(Consts P, Tables tb, const 
         wave_sync();
         cost += step_cost_wave(P, cl);
     }
+    if (keep.cost) {
+        // an elite's trial: kept where its window cost is lower (the batch
+        // slot then takes the replay's end of window, the trial's mass and
+        // friction, and its cost; flag = 1 asks for the gradient at the new
+        // start), otherwise the step is halved (flag = 0)
+        const bool kept = cost < keep.cost[i];
+        if (lane == 0) {
+            keep.flag[i] = kept ? 1 : 0;
+            if (kept) {
+                keep.cost[i] = cost;
+                keep.cost_sum[e] = cost;
+                keep.params[e] = B.m;
+                keep.params[(size_t)P.K + e] = B.mu;
+            } else {
+                keep.rho[i] *= 0.5f;
+            }
+        }
+        if (kept) {
+            if (lane < XI_ROWS) keep.xi[(size_t)lane * n + i] = xi[(size_t)lane * n + i];
+            store_body(keep.state, keep.params, P.K, e, B);   // f is 0 after a step
+            store_warm(keep.warm, P.C_max, e, wkey, wr);
+        }
+        return;
+    }
     if (lane == 0) {
         cost_out[i] = cost;
         if (resid_out) resid_out[i] = resid;
@@ -114,23 +144,59 @@ __global__ __launch_bounds__(WAVE) void k_window_fwd(Consts P, Tables tb, const 
     if (end_warm) store_warm(end_warm, P.C_max, i, wkey, wr);
 }
 
+// trial start of elite i: xi - rho (s o s o g) / |s o g| over (x, q, v, w, m,
+// mu), then q renormalised and m, mu clamped; the one-step force is kept
+__device__ __forceinline__ void refine_propose(const RefineTry &R, const float *__restrict__ xi,
+                                               const float (&grad)[XI_ROWS], int n, int i)
+{
+    const RefineArgs &A = R.args;
+    float x[XI_ROWS];
+    for (int r = 0; r < XI_ROWS; ++r) x[r] = xi[(size_t)r * n + i];
+    float sg2 = 0.f;
+    for (int r = 0; r < 15; ++r) {
+        float v = A.scale[r] * grad[r];
+        sg2 += v * v;
+    }
+    const float nrm = sqrtf(sg2);
+    if (nrm > 0.f && nrm < __int_as_float(0x7f800000)) {
+        const float f = R.rho[i] / nrm;
+        for (int r = 0; r < 15; ++r) x[r] -= f * A.scale[r] * A.scale[r] * grad[r];
+        const float qn = sqrtf(x[3] * x[3] + x[4] * x[4] + x[5] * x[5] + x[6] * x[6]);
+        if (qn > 0.f)
+            for (int r = 3; r < 7; ++r) x[r] /= qn;
+        x[13] = fminf(fmaxf(x[13], A.m_lo), A.m_hi);
+        x[14] = fminf(fmaxf(x[14], A.mu_lo), A.mu_hi);
+    }
+    if (lane_id() == 0)
+        for (int r = 0; r < XI_ROWS; ++r) R.xi_try[(size_t)r * n + i] = x[r];
+}
+
 // reverse sweep over the checkpoints k_window_fwd wrote for the same n, env
 // and xi (ckpt_by_env = 0: slot c of the launch), or that the population's
 // window wrote (ckpt_by_env = 1: slot env[i]); simulations with flag[i] == 0
-// are skipped (flag may be NULL)
+// keep their gradient (flag may be NULL); with refine.xi_try the next trial
+// start is proposed from it, swept or kept
 template <typename SR>
 __global__ __launch_bounds__(WAVE) void k_window_bwd(Consts P, Tables tb, const float *__restrict__ seg_win, int n,
                                                      int i0, int count,
                                                      const int32_t *__restrict__ env, const float *__restrict__ xi,
                                                      const float *__restrict__ obs_gt_win,
                                                      const float *__restrict__ ckpt, int ckpt_by_env,
-                                                     const int32_t *__restrict__ flag, float *__restrict__ grad)
+                                                     const int32_t *__restrict__ flag, float *__restrict__ grad,
+                                                     RefineTry refine)
 {
     extern __shared__ __align__(16) char smem[];
     const int c = blockIdx.x;
     if (c >= count) return;
     const int i = i0 + c;
-    if (flag && flag[i] == 0) return;
+    if (flag && flag[i] == 0) {
+        if (refine.xi_try) {
+            float g[XI_ROWS];
+            for (int r = 0; r < XI_ROWS; ++r) g[r] = grad[(size_t)r * n + i];
+            refine_propose(refine, xi, g, n, i);
+        }
+        return;
+    }
     const int lane = lane_id();
     const int e = env[i];
     if (e < 0 || e >= P.K) {
@@ -179,101 +245,41 @@ __global__ __launch_bounds__(WAVE) void k_window_bwd(Consts P, Tables tb, const 
         step_adjoint<SR>(P, seg, sph, inv, B, st, obs_gt_win + (size_t)t * 4 * LG, g, stage, lds.wr,
                          reinterpret_cast<SR *>(lds.cand_d), bar, mbar, mubar, t == 0 ? fbar : nullptr);
     }
-    if (lane == 0) {
-        const SR gv[XI_ROWS] = {bar.x[0], bar.x[1], bar.x[2], bar.q[0], bar.q[1], bar.q[2], bar.q[3],
-                                bar.v[0], bar.v[1], bar.v[2], bar.w[0], bar.w[1], bar.w[2],
-                                mbar,     mubar,    fbar[0],  fbar[1],  fbar[2]};
-        for (int r = 0; r < XI_ROWS; ++r) grad[(size_t)r * n + i] = (float)gv[r];
-    }
+    const float gv[XI_ROWS] = {(float)bar.x[0], (float)bar.x[1], (float)bar.x[2], (float)bar.q[0], (float)bar.q[1],
+                               (float)bar.q[2], (float)bar.q[3], (float)bar.v[0], (float)bar.v[1], (float)bar.v[2],
+                               (float)bar.w[0], (float)bar.w[1], (float)bar.w[2], (float)mbar,     (float)mubar,
+                               (float)fbar[0],  (float)fbar[1],  (float)fbar[2]};
+    if (lane == 0)
+        for (int r = 0; r < XI_ROWS; ++r) grad[(size_t)r * n + i] = gv[r];
+    if (refine.xi_try) refine_propose(refine, xi, gv, n, i);
 }
 
 // start of each listed simulation from the window-start snapshot (and, if
-// cost_sum is given, its window cost)
-__global__ void k_refine_gather(int n, int K, int C_max, const int32_t *__restrict__ env,
-                                const float *__restrict__ state, const float *__restrict__ params,
-                                const float *__restrict__ warm, const float *__restrict__ cost_sum,
-                                float *__restrict__ xi, float *__restrict__ warm0, float *__restrict__ cost,
-                                float *__restrict__ rho, float rho0)
+// cost_sum is given, its window cost): one row entry or warm-cache slot per
+// thread
+__global__ __launch_bounds__(256) void k_refine_gather(int n, int K, int C_max, const int32_t *__restrict__ env,
+                                                       const float *__restrict__ state, const float *__restrict__ params,
+                                                       const float *__restrict__ warm, const float *__restrict__ cost_sum,
+                                                       float *__restrict__ xi, float *__restrict__ warm0,
+                                                       float *__restrict__ cost, float *__restrict__ rho, float rho0)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int e = env[i];
-    if (e < 0 || e >= K) return;
-    for (int r = 0; r < 13; ++r) xi[(size_t)r * n + i] = state[(size_t)r * K + e];
-    for (int r = 0; r < 5; ++r) xi[(size_t)(13 + r) * n + i] = params[(size_t)r * K + e];
-    const float4 *src = reinterpret_cast<const float4 *>(warm + (size_t)e * C_max * WARM_STRIDE);
-    float4 *dst = reinterpret_cast<float4 *>(warm0 + (size_t)i * C_max * WARM_STRIDE);
-    for (int c = 0; c < C_max; ++c) dst[c] = src[c];
-    rho[i] = rho0;
-    if (cost_sum) cost[i] = cost_sum[e];
-}
-
-// trial start: xi - rho (s o s o g) / |s o g| over (x, q, v, w, m, mu), then
-// q renormalised and m, mu clamped; the one-step force is kept (elites
-// i0 .. i0+count-1 of arrays with row stride n)
-__global__ void k_refine_propose(int n, int i0, int count, RefineArgs A, const float *__restrict__ xi,
-                                 const float *__restrict__ grad, const float *__restrict__ rho,
-                                 float *__restrict__ xi_try)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= count) return;
-    const int i = i0 + c;
-    float x[XI_ROWS];
-    for (int r = 0; r < XI_ROWS; ++r) x[r] = xi[(size_t)r * n + i];
-    float sg2 = 0.f;
-    for (int r = 0; r < 15; ++r) {
-        float v = A.scale[r] * grad[(size_t)r * n + i];
-        sg2 += v * v;
+    const int rows = XI_ROWS * n, total = rows + n * C_max;
+    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < total; x += gridDim.x * blockDim.x) {
+        const bool row = x < rows;
+        const int i = row ? x % n : (x - rows) / C_max, r = row ? x / n : x - rows - i * C_max;
+        const int e = env[i];
+        if (e < 0 || e >= K) continue;
+        if (!row) {
+            reinterpret_cast<float4 *>(warm0)[(size_t)i * C_max + r] =
+                reinterpret_cast<const float4 *>(warm)[(size_t)e * C_max + r];
+            continue;
+        }
+        xi[x] = r < 13 ? state[(size_t)r * K + e] : params[(size_t)(r - 13) * K + e];
+        if (r == 0) {
+            rho[i] = rho0;
+            if (cost_sum) cost[i] = cost_sum[e];
+        }
     }
-    const float nrm = sqrtf(sg2);
-    if (nrm > 0.f && nrm < __int_as_float(0x7f800000)) {
-        const float f = rho[i] / nrm;
-        for (int r = 0; r < 15; ++r) x[r] -= f * A.scale[r] * A.scale[r] * grad[(size_t)r * n + i];
-        const float qn = sqrtf(x[3] * x[3] + x[4] * x[4] + x[5] * x[5] + x[6] * x[6]);
-        if (qn > 0.f)
-            for (int r = 3; r < 7; ++r) x[r] /= qn;
-        x[13] = fminf(fmaxf(x[13], A.m_lo), A.m_hi);
-        x[14] = fminf(fmaxf(x[14], A.mu_lo), A.mu_hi);
-    }
-    for (int r = 0; r < XI_ROWS; ++r) xi_try[(size_t)r * n + i] = x[r];
-}
-
-// keep the trial where its replayed window cost is lower (the batch slot then
-// takes the replay's end-of-window state, mass, friction and warm cache, and
-// its window cost; flag[i] = 1 asks for the gradient at the new start);
-// otherwise halve the step (flag[i] = 0); elites i0 .. i0+count-1
-__global__ void k_refine_accept(int n, int i0, int count, int K, int C_max, const int32_t *__restrict__ env,
-                                float *__restrict__ cost_cur,
-                                const float *__restrict__ cost_try, float *__restrict__ xi,
-                                const float *__restrict__ xi_try, float *__restrict__ rho, int32_t *__restrict__ flag,
-                                const float *__restrict__ end_state, const float *__restrict__ end_warm,
-                                float *__restrict__ state, float *__restrict__ params, float *__restrict__ warm,
-                                float *__restrict__ cost_sum)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= count) return;
-    const int i = i0 + c;
-    flag[i] = 0;
-    const int e = env[i];
-    if (e < 0 || e >= K) return;
-    const float ct = cost_try[i];
-    if (!(ct < cost_cur[i])) {
-        rho[i] *= 0.5f;
-        return;
-    }
-    flag[i] = 1;
-    cost_cur[i] = ct;
-    for (int r = 0; r < XI_ROWS; ++r) xi[(size_t)r * n + i] = xi_try[(size_t)r * n + i];
-    for (int r = 0; r < 13; ++r) state[(size_t)r * K + e] = end_state[(size_t)r * n + i];
-    params[0 * (size_t)K + e] = xi_try[13 * (size_t)n + i];
-    params[1 * (size_t)K + e] = xi_try[14 * (size_t)n + i];
-    params[2 * (size_t)K + e] = 0.f;
-    params[3 * (size_t)K + e] = 0.f;
-    params[4 * (size_t)K + e] = 0.f;
-    const float4 *src = reinterpret_cast<const float4 *>(end_warm + (size_t)i * C_max * WARM_STRIDE);
-    float4 *dst = reinterpret_cast<float4 *>(warm + (size_t)e * C_max * WARM_STRIDE);
-    for (int c = 0; c < C_max; ++c) dst[c] = src[c];
-    cost_sum[e] = ct;
 }
 
 }  // namespace pt
@@ -285,14 +291,14 @@ size_t ckpt_floats(const Consts &P, int n) { return (size_t)n * P.T * ckpt_step_
 hipError_t launch_window_fwd(const Consts &P, const Tables &tb, const float *seg_win, int n, int i0, int count,
                              const int32_t *env, const float *xi, const float *warm0, const float *obs_gt_win,
                              float *cost, float *end_state, float *end_warm, float *ckpt, hipStream_t s,
-                             float *resid)
+                             float *resid, const RefineKeep *keep)
 {
     if (count <= 0) return hipSuccess;
     size_t lds = wave_lds_bytes(P.max_cand, 0);
     // paired line-search trials when no step can hold more than 32 contacts
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(count), dim3(WAVE), lds, s, P, tb, seg_win, n, i0, count, env, xi, warm0,
-                           obs_gt_win, cost, end_state, end_warm, ckpt, resid);
+                           obs_gt_win, cost, end_state, end_warm, ckpt, resid, keep ? *keep : RefineKeep());
         return hipGetLastError();
     };
     const bool pt = P.C_max <= 32;
@@ -302,17 +308,18 @@ hipError_t launch_window_fwd(const Consts &P, const Tables &tb, const float *seg
 
 hipError_t launch_window_bwd(const Consts &P, const Tables &tb, const float *seg_win, int n, int i0, int count,
                              const int32_t *env, const float *xi, const float *obs_gt_win, const float *ckpt,
-                             bool ckpt_by_env, const int32_t *flag, float *grad, hipStream_t s)
+                             bool ckpt_by_env, const int32_t *flag, float *grad, hipStream_t s, const RefineTry *refine)
 {
     if (count <= 0) return hipSuccess;
     size_t lds = wave_lds_bytes(P.max_cand_rows, 0);
     const int by_env = ckpt_by_env ? 1 : 0;
+    const RefineTry next = refine ? *refine : RefineTry();
     if (P.solve_fp64)
         hipLaunchKernelGGL(k_window_bwd<double>, dim3(count), dim3(WAVE), lds, s, P, tb, seg_win, n, i0, count, env,
-                           xi, obs_gt_win, ckpt, by_env, flag, grad);
+                           xi, obs_gt_win, ckpt, by_env, flag, grad, next);
     else
         hipLaunchKernelGGL(k_window_bwd<float>, dim3(count), dim3(WAVE), lds, s, P, tb, seg_win, n, i0, count, env,
-                           xi, obs_gt_win, ckpt, by_env, flag, grad);
+                           xi, obs_gt_win, ckpt, by_env, flag, grad, next);
     return hipGetLastError();
 }
 
@@ -321,28 +328,9 @@ hipError_t launch_refine_gather(int n, int K, int C_max, const int32_t *env, con
                                 float *rho, float rho0, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_refine_gather, dim3((n + 63) / 64), dim3(64), 0, s, n, K, C_max, env, state, params, warm,
+    hipLaunchKernelGGL(k_refine_gather, dim3(std::min<size_t>(((size_t)n * (XI_ROWS + C_max) + 255) / 256, 4096)),
+                       dim3(256), 0, s, n, K, C_max, env, state, params, warm,
                        cost_sum, xi, warm0, cost, rho, rho0);
-    return hipGetLastError();
-}
-
-hipError_t launch_refine_propose(int n, int i0, int count, const RefineArgs &A, const float *xi, const float *grad,
-                                 const float *rho, float *xi_try, hipStream_t s)
-{
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_refine_propose, dim3((count + 63) / 64), dim3(64), 0, s, n, i0, count, A, xi, grad, rho,
-                       xi_try);
-    return hipGetLastError();
-}
-
-hipError_t launch_refine_accept(int n, int i0, int count, int K, int C_max, const int32_t *env, float *cost_cur,
-                                const float *cost_try, float *xi, const float *xi_try, float *rho, int32_t *flag,
-                                const float *end_state, const float *end_warm, float *state, float *params,
-                                float *warm, float *cost_sum, hipStream_t s)
-{
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_refine_accept, dim3((count + 63) / 64), dim3(64), 0, s, n, i0, count, K, C_max, env,
-                       cost_cur, cost_try, xi, xi_try, rho, flag, end_state, end_warm, state, params, warm, cost_sum);
     return hipGetLastError();
 }
 

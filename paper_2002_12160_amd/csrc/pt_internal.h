@@ -25,6 +25,22 @@ struct RefineArgs {
     float m_lo, m_hi, mu_lo, mu_hi;
 };
 
+// what a forward sweep over elites' trials does with them (cost NULL: no
+// trials): the elites' costs, starts, steps and flags, and the batch's own
+// buffers for the kept ones' end of window
+struct RefineKeep {
+    float *cost = nullptr, *xi = nullptr, *rho = nullptr;
+    int32_t *flag = nullptr;
+    float *state = nullptr, *params = nullptr, *warm = nullptr, *cost_sum = nullptr;
+};
+
+// the next trial starts a reverse sweep over elites proposes (xi_try NULL: none)
+struct RefineTry {
+    RefineArgs args = {};
+    const float *rho = nullptr;
+    float *xi_try = nullptr;
+};
+
 // populations up to this size rank their groups in the last workgroup of the
 // cost or window kernel instead of a launch of their own
 constexpr int FUSED_ARGMIN_MAX = 4096;
@@ -129,20 +145,14 @@ size_t ckpt_floats(const pt::Consts &P, int n);
 hipError_t launch_window_fwd(const pt::Consts &P, const pt::Tables &tb, const float *seg_win, int n, int i0,
                              int count, const int32_t *env, const float *xi, const float *warm0,
                              const float *obs_gt_win, float *cost, float *end_state, float *end_warm, float *ckpt,
-                             hipStream_t s, float *resid = nullptr);
+                             hipStream_t s, float *resid = nullptr, const pt::RefineKeep *keep = nullptr);
 hipError_t launch_window_bwd(const pt::Consts &P, const pt::Tables &tb, const float *seg_win, int n, int i0,
                              int count, const int32_t *env, const float *xi, const float *obs_gt_win,
                              const float *ckpt, bool ckpt_by_env, const int32_t *flag, float *grad,
-                             hipStream_t s);
+                             hipStream_t s, const pt::RefineTry *refine = nullptr);
 hipError_t launch_refine_gather(int n, int K, int C_max, const int32_t *env, const float *state, const float *params,
                                 const float *warm, const float *cost_sum, float *xi, float *warm0, float *cost,
                                 float *rho, float rho0, hipStream_t s);
-hipError_t launch_refine_propose(int n, int i0, int count, const pt::RefineArgs &A, const float *xi,
-                                 const float *grad, const float *rho, float *xi_try, hipStream_t s);
-hipError_t launch_refine_accept(int n, int i0, int count, int K, int C_max, const int32_t *env, float *cost_cur,
-                                const float *cost_try, float *xi, const float *xi_try, float *rho, int32_t *flag,
-                                const float *end_state, const float *end_warm, float *state, float *params,
-                                float *warm, float *cost_sum, hipStream_t s);
 hipError_t launch_weighted_resample(const pt::Consts &P, const pt::ResampleArgs &R, int kind, float hyper,
                                     const int32_t *group_start, int max_group, int n_steps, uint32_t window_idx,
                                     float *cost_sum, float *state, float *params, float *warm, float *snap,
