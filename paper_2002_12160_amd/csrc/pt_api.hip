@@ -96,7 +96,7 @@ struct pt_batch_s {
     int device;
     int num_cu;
     // device tables
-    float *d_hand = nullptr, *d_spheres = nullptr, *d_inv = nullptr;
+    float *d_hand = nullptr, *d_spheres = nullptr, *d_inv = nullptr, *d_reach = nullptr;
     int32_t *d_nsph = nullptr, *d_type = nullptr, *d_group_of = nullptr, *d_group_start = nullptr;
     int32_t *d_order = nullptr, *d_queue = nullptr;
     int64_t *d_stats = nullptr;
@@ -492,6 +492,14 @@ pt_status pt_create_batch(const pt_batch_desc *d, pt_batch *out)
     std::vector<int32_t> group_of(K), order(K);
     for (int g = 0; g < d->G; ++g)
         for (int i = d->group_start[g]; i < d->group_start[g + 1]; ++i) group_of[i] = g;
+    // how far an object's spheres reach from its centre, rounded up
+    std::vector<float> reach(d->n_types, 0.f);
+    for (int t = 0; t < d->n_types; ++t)
+        for (int i = 0; i < d->n_spheres[t]; ++i) {
+            const float *q = d->spheres + 4 * ((size_t)t * d->S_max + i);
+            const double r = std::sqrt((double)q[0] * q[0] + (double)q[1] * q[1] + (double)q[2] * q[2]) + q[3];
+            reach[t] = std::max(reach[t], (float)(r * (1.0 + 1e-6)));
+        }
     // persistent-kernel work order: simulations with more spheres first
     for (size_t i = 0; i < K; ++i) order[i] = (int32_t)i;
     std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
@@ -501,6 +509,7 @@ pt_status pt_create_batch(const pt_batch_desc *d, pt_batch *out)
     HIP_TRY_C(hipMalloc(&b->d_hand, sizeof(float) * d->L * PT_HAND_STRIDE));
     HIP_TRY_C(hipMalloc(&b->d_spheres, sizeof(float) * d->n_types * d->S_max * 4));
     HIP_TRY_C(hipMalloc(&b->d_inv, sizeof(float) * d->n_types * 3));
+    HIP_TRY_C(hipMalloc(&b->d_reach, sizeof(float) * d->n_types));
     HIP_TRY_C(hipMalloc(&b->d_nsph, sizeof(int32_t) * d->n_types));
     HIP_TRY_C(hipMalloc(&b->d_type, sizeof(int32_t) * K));
     HIP_TRY_C(hipMalloc(&b->d_group_of, sizeof(int32_t) * K));
@@ -555,6 +564,7 @@ pt_status pt_create_batch(const pt_batch_desc *d, pt_batch *out)
     }
     HIP_TRY_C(hipMemcpy(b->d_hand, d->hand, sizeof(float) * d->L * PT_HAND_STRIDE, hipMemcpyHostToDevice));
     HIP_TRY_C(hipMemcpy(b->d_spheres, d->spheres, sizeof(float) * d->n_types * d->S_max * 4, hipMemcpyHostToDevice));
+    HIP_TRY_C(hipMemcpy(b->d_reach, reach.data(), sizeof(float) * d->n_types, hipMemcpyHostToDevice));
     HIP_TRY_C(hipMemcpy(b->d_inv, d->inv_inertia, sizeof(float) * d->n_types * 3, hipMemcpyHostToDevice));
     HIP_TRY_C(hipMemcpy(b->d_nsph, d->n_spheres, sizeof(int32_t) * d->n_types, hipMemcpyHostToDevice));
     HIP_TRY_C(hipMemcpy(b->d_type, d->env_type, sizeof(int32_t) * K, hipMemcpyHostToDevice));
@@ -599,7 +609,7 @@ pt_status pt_destroy_batch(pt_batch b)
         if (b->ev_join[k]) (void)hipEventDestroy(b->ev_join[k]);
     }
     if (b->ev_fork) (void)hipEventDestroy(b->ev_fork);
-    void *ptrs[] = {b->d_hand, b->d_spheres, b->d_inv, b->d_nsph, b->d_type, b->d_group_of, b->d_group_start,
+    void *ptrs[] = {b->d_hand, b->d_spheres, b->d_inv, b->d_reach, b->d_nsph, b->d_type, b->d_group_of, b->d_group_start,
                     b->d_order, b->d_queue, b->d_stats, b->d_seg_win, b->d_contacts,
                     b->d_seg_grad, b->d_tune, b->d_ckpt, b->d_wckpt, b->d_elite, b->d_ref, b->d_snap,
                     b->d_elite_start, b->d_rank, b->d_by_rank, b->d_pieces, b->d_cslip, b->d_seg, b->d_pd, b->d_parent, b->d_pd_obs, b->d_sdf, b->d_sdf_box};
@@ -616,6 +626,7 @@ static Tables tables_of(const pt_batch b)
     tb.spheres = b->d_spheres;
     tb.n_spheres = b->d_nsph;
     tb.inv_inertia = b->d_inv;
+    tb.reach = b->d_reach;
     tb.env_type = b->d_type;
     tb.group_of = b->d_group_of;
     tb.sdf = b->d_sdf;

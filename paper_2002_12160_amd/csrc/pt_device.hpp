@@ -18,6 +18,13 @@ constexpr int WAVE = 64;
 constexpr int SEG_STRIDE = 16;  // per-link hand segment record, floats
 constexpr int WARM_STRIDE = 4;  // key bits + r(3)
 
+// the words after a wave's candidate list: 64 of its own (sel), the
+// warm-cache lookup and the contact stage.  The narrow phase stages the links
+// there, before the lookup is written; nothing reads them between the warm
+// start and the end of a step's solve, so the solve's sum rows may run on
+// into them
+constexpr int WAVE_SPARE_BYTES = 4 * 64 + 4 * 64 + 12 * 64 + 16 * 64;
+
 // ---------------------------------------------------------------------
 // constants of a batch, passed by value to every kernel
 // ---------------------------------------------------------------------
@@ -37,6 +44,7 @@ struct Tables {
     const float *spheres;       // [n_types][S_max][4]
     const int32_t *n_spheres;   // [n_types]
     const float *inv_inertia;   // [n_types][3]
+    const float *reach;         // [n_types] how far any sphere reaches from the object's centre
     const int32_t *env_type;    // [K]
     const int32_t *group_of;    // [K]
     const float *sdf;           // [n_types][sdf_n^3] distance-field nodes (collision_mode 1)
@@ -51,9 +59,8 @@ struct Body {
 
 // per-wave LDS scratch
 struct WaveLds {
-    float *cand_d;   // [max_cand]
-    int *cand_k;     // [max_cand]
-    int *sel;        // [64]
+    uint64_t *cand;  // [max_cand] candidate list: packed (gap, key) words
+    int *sel;        // [64] (the narrow phase stages the links from here on, the step's other arrays being free)
     int *wkey;       // [64]
     float *wr;       // [64*3]
     float *seg;      // [L][16] hand segment records of the step (after the [64][4] contact stage)
@@ -165,12 +172,6 @@ __device__ __forceinline__ uint64_t pack_gap_key(float d, int k)
     return ((uint64_t)u << 32) | (uint32_t)k;
 }
 
-// the gap whose packed word's upper half is u
-__device__ __forceinline__ float unpack_gap(uint32_t u)
-{
-    return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
-}
-
 // One half-wave's values in both halves: lanes i and i + 32 both end with
 // what lane i held (from_upper false) or what lane i + 32 held (true).  One
 // ds_bpermute per 32-bit word (the LDS crossbar, no LDS memory).
@@ -247,6 +248,67 @@ __device__ __forceinline__ T wave_sum1(T a, int span = 64)
     return v[0];
 }
 
+// Bitonic sort of one packed word per lane, ascending over the wavefront (n
+// <= 64 words in the first n lanes, the others the largest word): partners in
+// a row by DPP, across rows by the gfx950 lane swaps, five to nine
+// instructions an exchange and no LDS.  16 and 32 words skip the later stages.
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp_w(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, 0xf, 0xf, true);
+    return ((uint64_t)hi << 32) | lo;
+}
+// v of the lane 16 away in the pair of rows / 32 away
+__device__ __forceinline__ uint64_t swap_rows(uint64_t v, bool odd)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+    return odd ? ((uint64_t)hi[0] << 32) | lo[0] : ((uint64_t)hi[1] << 32) | lo[1];
+}
+__device__ __forceinline__ uint64_t swap_halves(uint64_t v, bool upper)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(v >> 32), (uint32_t)(v >> 32), false, false);
+    return upper ? ((uint64_t)hi[0] << 32) | lo[0] : ((uint64_t)hi[1] << 32) | lo[1];
+}
+// the smaller of the lane's word and its partner's, or the larger
+__device__ __forceinline__ uint64_t sort_pick(uint64_t v, uint64_t partner, bool larger)
+{
+    return (partner < v) != larger ? partner : v;
+}
+__device__ __forceinline__ uint64_t wave_sort(uint64_t v, int n)
+{
+    const int lane = lane_here();
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8, b4 = lane & 16, b5 = lane & 32;
+    const auto by4 = [&](uint64_t x) { return dpp_w<0x1b>(dpp_w<0x141>(x)); };   // half mirror, then reversed fours
+    const auto in8 = [&] {
+        v = sort_pick(v, by4(v), b2);
+        v = sort_pick(v, dpp_w<0x4e>(v), b1);
+        v = sort_pick(v, dpp_w<0xb1>(v), b0);
+    };
+    v = sort_pick(v, dpp_w<0xb1>(v), b0);                  // pairs
+    v = sort_pick(v, dpp_w<0x1b>(v), b1);                  // fours: mirrored, then pairs
+    v = sort_pick(v, dpp_w<0xb1>(v), b0);
+    v = sort_pick(v, dpp_w<0x141>(v), b2);                 // eights
+    v = sort_pick(v, dpp_w<0x4e>(v), b1);
+    v = sort_pick(v, dpp_w<0xb1>(v), b0);
+    v = sort_pick(v, dpp_w<0x140>(v), b3);                 // rows of 16
+    in8();
+    if (n > 16) {
+        v = sort_pick(v, swap_rows(dpp_w<0x140>(v), b4), b4);
+        v = sort_pick(v, dpp_w<0x128>(v), b3);             // row_ror:8
+        in8();
+    }
+    if (n > 32) {
+        v = sort_pick(v, swap_halves(swap_rows(dpp_w<0x140>(v), b4), b5), b5);
+        v = sort_pick(v, swap_rows(v, b4), b4);
+        v = sort_pick(v, dpp_w<0x128>(v), b3);
+        in8();
+    }
+    return v;
+}
+
 // span of lanes holding the first n contacts
 __device__ __forceinline__ int lane_span(int n) { return n <= 16 ? 16 : (n <= 32 ? 32 : 64); }
 
@@ -305,14 +367,19 @@ __device__ __forceinline__ void quat_mul_d(const double *a, const double *b, dou
 // hand segment record (16 floats): a(3), radius, ab(3), 1/|ab|^2 (0 if
 // degenerate), va(3), 0, vb(3), 0  -- positions at the start of the step,
 // endpoint velocities over the step.
-// gap of sphere (c, rho) to the capsule whose record starts at s
-__device__ __forceinline__ float segment_gap(const float *s, const float *c, float rho)
+// squared distance of point c to the axis of the capsule whose record starts
+// at s, and the gap of sphere (c, rho) to the capsule
+__device__ __forceinline__ float segment_dist2(const float *s, const float *c)
 {
     float ca0 = c[0] - s[0], ca1 = c[1] - s[1], ca2 = c[2] - s[2];
     float t = (ca0 * s[4] + ca1 * s[5] + ca2 * s[6]) * s[7];
     t = fminf(fmaxf(t, 0.f), 1.f);
     float d0 = ca0 - t * s[4], d1 = ca1 - t * s[5], d2 = ca2 - t * s[6];
-    return sqrtf(d0 * d0 + d1 * d1 + d2 * d2) - rho - s[3];
+    return d0 * d0 + d1 * d1 + d2 * d2;
+}
+__device__ __forceinline__ float segment_gap(const float *s, const float *c, float rho)
+{
+    return sqrtf(segment_dist2(s, c)) - rho - s[3];
 }
 
 __device__ __forceinline__ float pair_gap(const float *__restrict__ seg, int l, int L, const float *c, float rho)

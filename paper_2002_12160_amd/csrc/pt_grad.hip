@@ -67,6 +67,7 @@ __global__ __launch_bounds__(WAVE) void k_window_fwd(Consts P, Tables tb, const 
     const int g = tb.group_of[e];
     const int S = tb.n_spheres[type];
     const float *sph = tb.spheres + (size_t)type * P.S_max * 4;
+    const float reach = tb.reach[type];
     const float inv[3] = {tb.inv_inertia[3 * type], tb.inv_inertia[3 * type + 1], tb.inv_inertia[3 * type + 2]};
     const size_t LG = (size_t)P.L * P.G;
     const size_t CK = ckpt_step_floats(P.C_max);
@@ -87,8 +88,8 @@ __global__ __launch_bounds__(WAVE) void k_window_fwd(Consts P, Tables tb, const 
         if (ck) save_body(ck, B);
         const float *seg = seg_win + (size_t)t * P.L * SEG_STRIDE;
         StepState<SR> st;
-        step_setup<SR>(P, seg, sph, S, inv, B, wkey, wr, lds, stt, st);
-        step_solve<SR, PT>(P, st, B.mu, inv, reinterpret_cast<SR *>(lds.cand_d));
+        step_setup<SR>(P, seg, sph, S, inv, B, reach, wkey, wr, lds, stt, st);
+        step_solve<SR, PT>(P, st, B.mu, inv, reinterpret_cast<SR *>(lds.cand));
         resid = fmaxf(resid, (float)st.psi_end);
         if (ck) save_contact<SR>(ck, P.C_max, st);
         int link;
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(WAVE) void k_window_fwd(Consts P, Tables tb, const 
         wave_sync();
         float o[4];
         float cl = 0.f;
-        if (sensor_force(P, stage, o)) {
+        if (sensor_force(P, stage, link, o)) {
             const float *gt = obs_gt_win + (size_t)t * 4 * LG;
             float gv[4] = {gt[0 * LG + (size_t)lane * P.G + g], gt[1 * LG + (size_t)lane * P.G + g],
                            gt[2 * LG + (size_t)lane * P.G + g], gt[3 * LG + (size_t)lane * P.G + g]};
@@ -243,7 +244,7 @@ __global__ __launch_bounds__(WAVE) void k_window_bwd(Consts P, Tables tb, const 
         st.nu[0] += st.vs[0]; st.nu[1] += st.vs[1]; st.nu[2] += st.vs[2];
         st.nu[3] += st.ws[0]; st.nu[4] += st.ws[1]; st.nu[5] += st.ws[2];
         step_adjoint<SR>(P, seg, sph, inv, B, st, obs_gt_win + (size_t)t * 4 * LG, g, stage, lds.wr,
-                         reinterpret_cast<SR *>(lds.cand_d), bar, mbar, mubar, t == 0 ? fbar : nullptr);
+                         reinterpret_cast<SR *>(lds.cand), bar, mbar, mubar, t == 0 ? fbar : nullptr);
     }
     const float gv[XI_ROWS] = {(float)bar.x[0], (float)bar.x[1], (float)bar.x[2], (float)bar.q[0], (float)bar.q[1],
                                (float)bar.q[2], (float)bar.q[3], (float)bar.v[0], (float)bar.v[1], (float)bar.v[2],

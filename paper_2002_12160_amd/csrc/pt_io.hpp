@@ -23,8 +23,7 @@ __device__ __forceinline__ WaveLds carve_lds(char *base, int wave_in_block, int 
 {
     char *p = base + (size_t)wave_in_block * wave_lds_bytes(max_cand, L);
     WaveLds w;
-    w.cand_d = reinterpret_cast<float *>(p);
-    w.cand_k = reinterpret_cast<int *>(p + 4 * (size_t)max_cand);
+    w.cand = reinterpret_cast<uint64_t *>(p);
     w.sel = reinterpret_cast<int *>(p + 8 * (size_t)max_cand);
     w.wkey = w.sel + WAVE;
     w.wr = reinterpret_cast<float *>(w.wkey + WAVE);
@@ -120,19 +119,44 @@ __device__ __forceinline__ void flush_stats(int64_t *stats, const StepStats &st,
     }
 }
 
-// per-sensor force from the contacts staged in LDS ([64][4]: link bits,
-// impulse on the object), summed in contact order; lane l < L gets
-// (|c_l|, c_hat_l).  Returns false on lanes >= L.
-__device__ __forceinline__ bool sensor_force(const Consts &P, const float *stage, float *o)
+// Calls f(i, rec, ...) for the staged contacts of sensors (bits of on), in
+// contact order, four contacts' LDS reads in flight: the next contacts in
+// order are found by scalar bit scans, every lane reads them all (broadcast)
+// and f adds what is its own.
+template <typename Read, typename Add>
+__device__ __forceinline__ void for_contacts(uint64_t on, Read read, Add add)
 {
-    const int lane = lane_id();
-    float f0 = 0.f, f1 = 0.f, f2 = 0.f;
-    for (int c = 0; c < P.C_max; ++c) {
-        const float4 rec = *reinterpret_cast<const float4 *>(stage + 4 * c);
-        if (__float_as_int(rec.x) == lane) {
-            f0 += rec.y; f1 += rec.z; f2 += rec.w;
+    while (on) {
+        decltype(read(0)) r[4];
+        bool has[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            has[i] = on != 0;
+            r[i] = read(has[i] ? __builtin_ctzll(on) : 0);
+            on &= on - 1;
         }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (has[i]) add(r[i]);
     }
+}
+
+// per-sensor force from the contacts staged in LDS ([64][4]: link bits,
+// impulse on the object), summed in contact order; link: this lane's staged
+// contact's (-1: none, or the table); lane l < L gets (|c_l|, c_hat_l).
+// Returns false on lanes >= L.
+__device__ __forceinline__ bool sensor_force(const Consts &P, const float *stage, int link, float *o)
+{
+    const int lane = lane_here();
+    float f0 = 0.f, f1 = 0.f, f2 = 0.f;
+    for_contacts(
+        __ballot(link >= 0), [&](int c) { return *reinterpret_cast<const float4 *>(stage + 4 * c); },
+        [&](const float4 &rec) {
+            const bool mine = __float_as_int(rec.x) == lane;
+            f0 += mine ? rec.y : 0.f;
+            f1 += mine ? rec.z : 0.f;
+            f2 += mine ? rec.w : 0.f;
+        });
     float idt = 1.f / P.dt;
     f0 = -f0 * idt; f1 = -f1 * idt; f2 = -f2 * idt;
     float mag = sqrtf(f0 * f0 + f1 * f1 + f2 * f2);
@@ -196,20 +220,31 @@ __device__ __forceinline__ void slip_record(const StepState<SR> &st, const float
 // normalised, when |s| > tau_slip, else 0; rot = the sign of
 // sum q / |sum r_n n| beyond tau_spin, else 0.  o[7].
 __device__ __forceinline__ bool sensor_obs_eq3(const Consts &P, const float *stage, const float *slip,
-                                               const float *seg, float *o)
+                                               const float *seg, int link, float *o)
 {
-    const int lane = lane_id();
-    const bool sensor = sensor_force(P, stage, o);
+    const int lane = lane_here();
+    const bool sensor = sensor_force(P, stage, link, o);
+    const uint64_t on = __ballot(link >= 0);
     o[4] = o[5] = o[6] = 0.f;
-    if (!sensor) return false;
     float N[3] = {0.f, 0.f, 0.f}, S[3] = {0.f, 0.f, 0.f}, W = 0.f, Q = 0.f;
-    for (int c = 0; c < P.C_max; ++c) {
-        if (__float_as_int(stage[4 * c]) != lane) continue;
-        const float4 a = *reinterpret_cast<const float4 *>(slip + SLIP_STRIDE * c);
-        const float4 b = *reinterpret_cast<const float4 *>(slip + SLIP_STRIDE * c + 4);
-        N[0] += a.x; N[1] += a.y; N[2] += a.z; W += a.w;
-        S[0] += b.x; S[1] += b.y; S[2] += b.z; Q += b.w;
-    }
+    struct Rec {
+        int link;
+        float4 a, b;
+    };
+    for_contacts(
+        on,
+        [&](int c) {
+            return Rec{__float_as_int(stage[4 * c]), *reinterpret_cast<const float4 *>(slip + SLIP_STRIDE * c),
+                       *reinterpret_cast<const float4 *>(slip + SLIP_STRIDE * c + 4)};
+        },
+        [&](const Rec &r) {
+            const bool mine = r.link == lane;
+            N[0] += mine ? r.a.x : 0.f; N[1] += mine ? r.a.y : 0.f; N[2] += mine ? r.a.z : 0.f;
+            W += mine ? r.a.w : 0.f;
+            S[0] += mine ? r.b.x : 0.f; S[1] += mine ? r.b.y : 0.f; S[2] += mine ? r.b.z : 0.f;
+            Q += mine ? r.b.w : 0.f;
+        });
+    if (!sensor) return false;
     const float nn = sqrtf(dot3(N, N));
     if (!(W > 0.f) || !(nn > 0.f)) return true;
     const float nb[3] = {N[0] / nn, N[1] / nn, N[2] / nn};

@@ -263,6 +263,7 @@ __global__ __launch_bounds__(StepBounds<SR>::threads) void k_step(Consts P, Tabl
     const int type = tb.env_type[e];
     const int S = tb.n_spheres[type];
     const float *sph = tb.spheres + (size_t)type * P.S_max * 4;
+    const float reach = tb.reach[type];
     const float inv[3] = {tb.inv_inertia[3 * type], tb.inv_inertia[3 * type + 1], tb.inv_inertia[3 * type + 2]};
     const float rows = load_body_rows(state, params, P.K, e);
     int wkey;
@@ -274,7 +275,7 @@ __global__ __launch_bounds__(StepBounds<SR>::threads) void k_step(Consts P, Tabl
     // as k_hand_fk
     if (!SEGIN)
         hand_kinematics(tb.hand, P.L, P.D, P.dt, u_prev, u,
-                        carve_fk(reinterpret_cast<char *>(lds.cand_d), P.L, P.D), lds.seg, lane_id(), WAVE,
+                        carve_fk(reinterpret_cast<char *>(lds.cand), P.L, P.D), lds.seg, lane_id(), WAVE,
                         [] { wave_sync(); });
     Body B;
     body_from_rows(rows, B);
@@ -290,8 +291,8 @@ __global__ __launch_bounds__(StepBounds<SR>::threads) void k_step(Consts P, Tabl
         sdf.n = P.sdf_n;
         sdf.M = P.link_samples;
     }
-    step_setup<SR, SDF>(P, seg, sph, S, inv, B, wkey, wr, lds, st, sst, sdf);
-    step_solve<SR, true>(P, sst, B.mu, inv, reinterpret_cast<SR *>(lds.cand_d));
+    step_setup<SR, SDF>(P, seg, sph, S, inv, B, reach, wkey, wr, lds, st, sst, sdf);
+    step_solve<SR, true>(P, sst, B.mu, inv, reinterpret_cast<SR *>(lds.cand));
     step_finish<SR>(P, sst, inv, B, wkey, wr, link, imp);
     const int lane = lane_id();
     if (EQ3) {
@@ -331,9 +332,11 @@ __global__ __launch_bounds__(256) void k_observe(Consts P, const float *__restri
     float *sg = stage[wib];
     float *sl = slip[wib];
     const bool eq3 = P.cost_mode == 1;
+    int link = -1;
     if (lane < P.C_max) {
-        *reinterpret_cast<float4 *>(sg + 4 * lane) =
-            *reinterpret_cast<const float4 *>(contacts + ((size_t)e * P.C_max + lane) * 4);
+        const float4 rec = *reinterpret_cast<const float4 *>(contacts + ((size_t)e * P.C_max + lane) * 4);
+        *reinterpret_cast<float4 *>(sg + 4 * lane) = rec;
+        link = __float_as_int(rec.x);
         if (eq3) {
             const float4 *src = reinterpret_cast<const float4 *>(cslip + ((size_t)e * P.C_max + lane) * SLIP_STRIDE);
             *reinterpret_cast<float4 *>(sl + SLIP_STRIDE * lane) = src[0];
@@ -343,7 +346,7 @@ __global__ __launch_bounds__(256) void k_observe(Consts P, const float *__restri
     wave_sync();
     const size_t LK = (size_t)P.L * P.K;
     float o[7];
-    const bool sensor = eq3 ? sensor_obs_eq3(P, sg, sl, seg, o) : sensor_force(P, sg, o);
+    const bool sensor = eq3 ? sensor_obs_eq3(P, sg, sl, seg, link, o) : sensor_force(P, sg, link, o);
     if (sensor) {
         const int R = eq3 ? 7 : 4;
 #pragma unroll
@@ -592,6 +595,7 @@ k_window(Consts P, Tables tb, const float *__restrict__ seg_win, float *__restri
         const int g = tb.group_of[e];
         const int S = tb.n_spheres[type];
         const float *sph = tb.spheres + (size_t)type * P.S_max * 4;
+        const float reach = tb.reach[type];
         const float inv[3] = {tb.inv_inertia[3 * type], tb.inv_inertia[3 * type + 1], tb.inv_inertia[3 * type + 2]};
         SdfRef sdf;
         if (SDF) {
@@ -616,8 +620,8 @@ k_window(Consts P, Tables tb, const float *__restrict__ seg_win, float *__restri
             float *ck = ckpt ? ckpt + ((size_t)e * P.T + t) * ckpt_step_floats(P.C_max) : nullptr;
             if (ck) save_body(ck, B);
             StepState<SR> sst;
-            step_setup<SR, SDF>(P, seg, sph, S, inv, B, wkey, wr, lds, st, sst, sdf);
-            step_solve<SR, PT>(P, sst, B.mu, inv, reinterpret_cast<SR *>(lds.cand_d));
+            step_setup<SR, SDF>(P, seg, sph, S, inv, B, reach, wkey, wr, lds, st, sst, sdf);
+            step_solve<SR, PT>(P, sst, B.mu, inv, reinterpret_cast<SR *>(lds.cand));
             if (ck) save_contact<SR>(ck, P.C_max, sst);
             step_finish<SR>(P, sst, inv, B, wkey, wr, link, imp);
             uniform_body(B);
@@ -625,7 +629,7 @@ k_window(Consts P, Tables tb, const float *__restrict__ seg_win, float *__restri
             // Eq. 3 (cost_mode 1): the contacts' slip records staged in the
             // candidate list's LDS, free between the solve and the next
             // step's narrow phase
-            float *slip = lds.cand_d;
+            float *slip = reinterpret_cast<float *>(lds.cand);
             if constexpr (EQ3) {
                 float rec[SLIP_STRIDE];
                 slip_record<SR>(sst, seg, B.w, rec);
@@ -636,7 +640,7 @@ k_window(Consts P, Tables tb, const float *__restrict__ seg_win, float *__restri
             float cl = 0.f;
             if constexpr (EQ3) {
                 float o[7];
-                if (sensor_obs_eq3(P, stage, slip, seg, o)) {
+                if (sensor_obs_eq3(P, stage, slip, seg, link, o)) {
                     const float *gt = obs_gt_win + (size_t)t * 7 * LG;
                     float gv[7];
 #pragma unroll
@@ -650,7 +654,7 @@ k_window(Consts P, Tables tb, const float *__restrict__ seg_win, float *__restri
                 }
             } else {
                 float o[4];
-                if (sensor_force(P, stage, o)) {
+                if (sensor_force(P, stage, link, o)) {
                     const float *gt = obs_gt_win + (size_t)t * 4 * LG;
                     float gv[4] = {gt[0 * LG + (size_t)lane * P.G + g], gt[1 * LG + (size_t)lane * P.G + g],
                                    gt[2 * LG + (size_t)lane * P.G + g], gt[3 * LG + (size_t)lane * P.G + g]};

@@ -39,6 +39,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2))) void 
     const int type = tb.env_type[e];
     const int S = tb.n_spheres[type];
     const float *sph = tb.spheres + (size_t)type * P.S_max * 4;
+    const float reach = tb.reach[type];
     const float inv[3] = {tb.inv_inertia[3 * type], tb.inv_inertia[3 * type + 1], tb.inv_inertia[3 * type + 2]};
     const float rows = load_body_rows(state, params, P.K, e);
     int wkey;
@@ -65,7 +66,7 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2))) void 
     }
     int link;
     float imp[3];
-    pd_step<SDF, G>(P, Q, tb, T, u, lds, pl, sph, S, inv, sdf, qv, B, wkey, wr, st, link, imp);
+    pd_step<SDF, G>(P, Q, tb, T, u, lds, pl, sph, S, inv, reach, sdf, qv, B, wkey, wr, st, link, imp);
     if (lane < D) {
         const double w = pl.nuh[lane];
         hstate[(size_t)jl * K + e] = (float)((double)qv + (double)P.dt * w);
@@ -109,6 +110,7 @@ __global__ __launch_bounds__(WAVE) void k_window_pd(Consts P, PdConsts Q, Tables
     const int g = tb.group_of[e];
     const int S = tb.n_spheres[type];
     const float *sph = tb.spheres + (size_t)type * P.S_max * 4;
+    const float reach = tb.reach[type];
     const float inv[3] = {tb.inv_inertia[3 * type], tb.inv_inertia[3 * type + 1], tb.inv_inertia[3 * type + 2]};
     const float rows = load_body_rows(state, params, P.K, e);
     int wkey;
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(WAVE) void k_window_pd(Consts P, PdConsts Q, Tables
         pd_stage_joints(D, pl, qv, qdv);
         int link;
         float imp[3];
-        pd_step<SDF, G>(P, Q, tb, T, u_win + (size_t)(t + 1) * D, lds, pl, sph, S, inv, sdf, qv, B, wkey, wr, st,
+        pd_step<SDF, G>(P, Q, tb, T, u_win + (size_t)(t + 1) * D, lds, pl, sph, S, inv, reach, sdf, qv, B, wkey, wr, st,
                         link, imp);
         if (lane < D) {
             const double w = pl.nuh[lane];
@@ -153,7 +155,7 @@ __global__ __launch_bounds__(WAVE) void k_window_pd(Consts P, PdConsts Q, Tables
         float *ob = obs_out ? obs_out + (size_t)t * RK : nullptr;
         float o[4];
         float cl = 0.f;
-        if (sensor_force(P, stage, o)) {
+        if (sensor_force(P, stage, link, o)) {
             float gv[4] = {gt[0 * LG + (size_t)lane * P.G + g], gt[1 * LG + (size_t)lane * P.G + g],
                            gt[2 * LG + (size_t)lane * P.G + g], gt[3 * LG + (size_t)lane * P.G + g]};
             cl = sensor_cost(P, o, gv);
@@ -190,13 +192,16 @@ __global__ __launch_bounds__(256) void k_observe_pd(Consts P, const float *__res
     if (e >= P.K) return;
     const int lane = lane_id();
     float *sg = stage[wib];
-    if (lane < P.C_max)
-        *reinterpret_cast<float4 *>(sg + 4 * lane) =
-            *reinterpret_cast<const float4 *>(contacts + ((size_t)e * P.C_max + lane) * 4);
+    int link = -1;
+    if (lane < P.C_max) {
+        const float4 rec = *reinterpret_cast<const float4 *>(contacts + ((size_t)e * P.C_max + lane) * 4);
+        *reinterpret_cast<float4 *>(sg + 4 * lane) = rec;
+        link = __float_as_int(rec.x);
+    }
     wave_sync();
     const size_t LK = (size_t)P.L * P.K;
     float o[7];
-    if (sensor_force(P, sg, o)) {
+    if (sensor_force(P, sg, link, o)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) obs[j * LK + (size_t)lane * P.K + e] = o[j];
     }

@@ -173,7 +173,7 @@ __device__ __forceinline__ PdLds carve_pd(char *p, int L, int D, const WaveLds &
     s.zh = d; d += D;
     s.nuh = d; d += D;
     s.linkrun = reinterpret_cast<int *>(d);
-    s.rows = reinterpret_cast<double *>(w.cand_d);
+    s.rows = reinterpret_cast<double *>(w.cand);
     s.sums = s.rows + PD_ROWS * RedStride<double>::value;
     s.tot = s.rows;
     s.acc = s.rows + 48;
@@ -887,16 +887,16 @@ __device__ __forceinline__ void pd_stage_joints(int D, const PdLds &pl, float q,
 template <bool SDF, int G>
 __device__ __forceinline__ void pd_step(const Consts &P, const PdConsts &Q, const Tables &tb, const PdTab &T,
                                         const float *__restrict__ u, const WaveLds &lds, const PdLds &pl,
-                                        const float *__restrict__ sph, int S, const float *inv, const SdfRef &sdf,
+                                        const float *__restrict__ sph, int S, const float *inv, float reach, const SdfRef &sdf,
                                         float q_lane, Body &B, int &wkey, float *wr, StepStats &stats, int &link,
                                         float *imp)
 {
-    double *fk = reinterpret_cast<double *>(lds.cand_d);
+    double *fk = reinterpret_cast<double *>(lds.cand);
     pd_fk(P, Q, T, tb.hand, fk, pl, lds.seg);
     pd_mass(P, Q, T, fk, pl, u, (double)q_lane);
     pd_twists(P.D, B.x, pl);
     StepState<double> sst;
-    step_setup<double, SDF>(P, lds.seg, sph, S, inv, B, wkey, wr, lds, stats, sst, sdf);
+    step_setup<double, SDF>(P, lds.seg, sph, S, inv, B, reach, wkey, wr, lds, stats, sst, sdf);
     int pos;
     uint64_t ends;
     pd_order_contacts(sst, pl, pos, ends);

@@ -192,29 +192,6 @@ __device__ __forceinline__ void contact_setup(const Consts &P, const float *__re
     }
 }
 
-// The cap's ranking for n <= 64 candidates: lane i holds candidate i as a
-// packed (d, key) word (lanes past n the largest word, never below a
-// candidate's, so the counts run over whole groups of four lanes); every
-// word is broadcast once and each lane counts the lower ones.  Keys are
-// unique, so the ranks are a permutation; the C_max lowest candidates' keys
-// land in sel[rank].
-__device__ __forceinline__ void cap_rank(const WaveLds &lds, int n, int C_max)
-{
-    const int lane = lane_here();
-    uint64_t w = ~0ull;
-    int ki = 0, rank = 0;
-    if (lane < n) {
-        ki = lds.cand_k[lane];
-        w = pack_gap_key(lds.cand_d[lane], ki);
-    }
-    for (int j = 0; j < n; j += 4) {
-        const uint64_t a = bcast_lane(w, j), b = bcast_lane(w, j + 1);
-        const uint64_t c = bcast_lane(w, j + 2), d = bcast_lane(w, j + 3);
-        rank += (a < w ? 1 : 0) + (b < w ? 1 : 0) + (c < w ? 1 : 0) + (d < w ? 1 : 0);
-    }
-    if (lane < n && rank < C_max) lds.sel[rank] = ki;
-}
-
 // Cuts the list's first n entries, C_max < n <= 64 H, to their C_max lowest
 // (d, key) entries, moved to its head in list order; returns the largest
 // kept packed word.  The boundary is found bit by bit (radix select: a bit
@@ -238,7 +215,7 @@ __device__ __forceinline__ uint64_t cap_cut(const WaveLds &lds, int n, int C_max
         const int i = lane + WAVE * h;
         hi[h] = lo[h] = ~0u;   // above every candidate: gaps are finite
         if (i < n) {
-            const uint64_t w = pack_gap_key(lds.cand_d[i], lds.cand_k[i]);
+            const uint64_t w = lds.cand[i];
             hi[h] = (uint32_t)(w >> 32);
             lo[h] = (uint32_t)w;
         }
@@ -290,8 +267,7 @@ __device__ __forceinline__ uint64_t cap_cut(const WaveLds &lds, int n, int C_max
         if (keep) {
             const int at = base + mask_rank(m);
             const uint64_t w = ((uint64_t)hi[h] << 32) | lo[h];
-            lds.cand_d[at] = unpack_gap(hi[h]);
-            lds.cand_k[at] = (int)lo[h];
+            lds.cand[at] = w;
             top = w > top ? w : top;
         }
         base += __popcll(m);
@@ -310,10 +286,7 @@ __device__ __forceinline__ int cap_cut_pieces(const WaveLds &lds, int n, int C_m
     while (n > PIECE) {
         cap_cut<8>(lds, PIECE, C_max);
         const int m = min(PIECE - C_max, n - PIECE);
-        for (int i = lane_id(); i < m; i += WAVE) {
-            lds.cand_d[C_max + i] = lds.cand_d[n - m + i];
-            lds.cand_k[C_max + i] = lds.cand_k[n - m + i];
-        }
+        for (int i = lane_id(); i < m; i += WAVE) lds.cand[C_max + i] = lds.cand[n - m + i];
         wave_sync();
         n = m < PIECE - C_max ? C_max + m : n - m;
     }
@@ -337,72 +310,73 @@ __device__ __forceinline__ int compact_candidates(const WaveLds &lds, int n, int
     return C_max;
 }
 
-// Narrow phase: lanes over spheres, candidates appended to LDS in (sphere
-// block, link) order by ballot + prefix count, the table (l == L) after the
-// links, two links' gaps at a time so that their arithmetic interleaves.
+// Narrow phase: lanes over spheres, two blocks of 64 at a time, links one by
+// one (two broadcast LDS reads of a staged record each), candidates appended
+// to LDS as packed words by ballot + prefix count, the table (l == L) after
+// the links; the list's order is of no account, the cap ranks it.
 // A link that no sphere can reach is skipped: a sphere's gap to a link is
 // at least the gap from the object centre x to the link less |c - x| + rho
 // (the distance to a segment is 1-Lipschitz), so a link farther from x than
-// the object's largest |c - x| + rho plus the margin (and 10 um for
-// rounding) holds no candidate; the reachable links are paired in
-// increasing order, so the candidates appended, and their order, are those
-// of the full loop.
-// Bounded: the list may fill up; when it may not hold another pair of links
-// and the table's candidates (3 x 64 entries; with no link in reach the table
-// alone cannot fill it) it is cut to its C_max lowest, and from then on only
+// the object's largest |c - x| + rho (reach) plus the margin (and 10 um for
+// rounding) holds no candidate.  So is the exact gap of a link none of the
+// 128 spheres has within the margin by the squared distance (1e-4 of slack,
+// a thousand times its rounding): no square root, no append.  Two thirds of
+// the real-time population's narrow phase were links read lane by lane, a
+// square root for every pair and one block's appends waiting for the other's.
+// Bounded: the list may fill up; when it may not hold another link's and the
+// table's candidates (4 x 64 entries; with no link in reach the table alone
+// cannot fill it) it is cut to its C_max lowest, and from then on only
 // candidates below the highest kept one are appended (removed counts the
 // others).
 template <bool Bounded>
 __device__ __forceinline__ void narrow_phase(const Consts &P, const WaveLds &lds, const float (&sgr)[8],
-                                             const float *__restrict__ sph, int S, const float *x, const float *R,
-                                             int cap, int &ncand, int &removed)
+                                             const float *__restrict__ sph, int S, float reach, const float *x,
+                                             const float *R, int cap, int &ncand, int &removed)
 {
     const int lane = lane_here();
     const int L = P.L;
     bool bar = false;
     uint64_t thr = 0;
-    // the links any sphere can reach (bit l; wave-uniform)
-    float reach = 0.f;
-    for (int k = lane; k < S; k += WAVE) {
-        const float4 t = *reinterpret_cast<const float4 *>(sph + 4 * k);
-        reach = fmaxf(reach, sqrtf(t.x * t.x + t.y * t.y + t.z * t.z) + t.w);
+    // the links' records (first 8 floats) staged for broadcast reads
+    float4 *links = reinterpret_cast<float4 *>(lds.sel);
+    static_assert(2 * 16 * 62 <= WAVE_SPARE_BYTES, "62 links' records in the spare words");
+    if (lane < L) {
+        links[2 * lane] = make_float4(sgr[0], sgr[1], sgr[2], sgr[3]);
+        links[2 * lane + 1] = make_float4(sgr[4], sgr[5], sgr[6], sgr[7]);
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) reach = fmaxf(reach, __shfl_xor(reach, o));
+    // the links any sphere can reach (bit l; wave-uniform)
     const uint64_t near = __ballot(lane < L && segment_gap(sgr, x, 0.f) - reach < P.margin + 1e-5f);
-    for (int kb = 0; kb < S; kb += WAVE) {
-        const int k = kb + lane;
-        const bool valid = k < S;
-        float s4[4] = {0.f, 0.f, 0.f, 0.f};
-        if (valid) {
-            const float4 t = *reinterpret_cast<const float4 *>(sph + 4 * k);
-            s4[0] = t.x; s4[1] = t.y; s4[2] = t.z; s4[3] = t.w;
-        }
-        const float c[3] = {x[0] + R[0] * s4[0] + R[1] * s4[1] + R[2] * s4[2],
-                            x[1] + R[3] * s4[0] + R[4] * s4[1] + R[5] * s4[2],
-                            x[2] + R[6] * s4[0] + R[7] * s4[1] + R[8] * s4[2]};
-        auto append = [&](float d, int l) {
+    wave_sync();
+    for (int kb = 0; kb < S; kb += 2 * WAVE) {
+        const int k0 = kb + lane, k1 = k0 + WAVE;
+        const bool two = kb + WAVE < S;   // wave-uniform
+        const float4 *s4 = reinterpret_cast<const float4 *>(sph);
+        const float4 t0 = s4[min(k0, S - 1)], t1 = s4[min(k1, S - 1)];
+        const float c0[3] = {x[0] + R[0] * t0.x + R[1] * t0.y + R[2] * t0.z,
+                             x[1] + R[3] * t0.x + R[4] * t0.y + R[5] * t0.z,
+                             x[2] + R[6] * t0.x + R[7] * t0.y + R[8] * t0.z};
+        const float c1[3] = {x[0] + R[0] * t1.x + R[1] * t1.y + R[2] * t1.z,
+                             x[1] + R[3] * t1.x + R[4] * t1.y + R[5] * t1.z,
+                             x[2] + R[6] * t1.x + R[7] * t1.y + R[8] * t1.z};
+        auto append = [&](bool valid, float d, int key) {
             bool cand = valid && (d < P.margin);
             uint64_t mask = __ballot(cand);
+            const uint64_t w = pack_gap_key(d, key);
             if constexpr (Bounded) {
                 if (bar) {
                     removed += __popcll(mask);
-                    cand = cand && pack_gap_key(d, k * (L + 1) + l) < thr;
+                    cand = cand && w < thr;
                     mask = __ballot(cand);
                     removed -= __popcll(mask);
                 }
             }
-            if (cand) {
-                const int pos = ncand + mask_rank(mask);
-                lds.cand_d[pos] = d;
-                lds.cand_k[pos] = k * (L + 1) + l;
-            }
+            if (cand) lds.cand[ncand + mask_rank(mask)] = w;
             ncand += __popcll(mask);
         };
-        // the reachable links in increasing order, two at a time
-        for (uint64_t m = near; m;) {
+        const float m0 = P.margin + t0.w, m1 = P.margin + t1.w;
+        for (uint64_t m = near; m; m &= m - 1) {
             if constexpr (Bounded) {
-                if (ncand + 3 * WAVE > cap) {
+                if (ncand + 4 * WAVE > cap) {
                     removed += ncand;
                     ncand = compact_candidates(lds, ncand, P.C_max, thr);
                     removed -= ncand;
@@ -410,20 +384,16 @@ __device__ __forceinline__ void narrow_phase(const Consts &P, const WaveLds &lds
                 }
             }
             const int l = __builtin_ctzll(m);
-            m &= m - 1;
-            const int l1 = m ? __builtin_ctzll(m) : l;
-            if (m) m &= m - 1;
-            float sa[8], sb[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                sa[i] = bcast_lane(sgr[i], l);
-                sb[i] = bcast_lane(sgr[i], l1);
-            }
-            const float da = segment_gap(sa, c, s4[3]), db = segment_gap(sb, c, s4[3]);
-            append(da, l);
-            if (l1 != l) append(db, l1);
+            const float4 a = links[2 * l], b = links[2 * l + 1];
+            const float sg[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+            const float q0 = segment_dist2(sg, c0), q1 = two ? segment_dist2(sg, c1) : 0.f;
+            const float r0 = m0 + sg[3], r1 = m1 + sg[3];
+            if (!__any(q0 < r0 * r0 * 1.0001f || (two && q1 < r1 * r1 * 1.0001f))) continue;
+            append(k0 < S, sqrtf(q0) - t0.w - sg[3], k0 * (L + 1) + l);
+            if (two) append(k1 < S, sqrtf(q1) - t1.w - sg[3], k1 * (L + 1) + l);
         }
-        append(c[2] - s4[3], L);
+        append(k0 < S, c0[2] - t0.w, k0 * (L + 1) + L);
+        if (two) append(k1 < S, c1[2] - t1.w, k1 * (L + 1) + L);
     }
 }
 
@@ -439,11 +409,7 @@ __device__ __forceinline__ void narrow_phase_sdf(const Consts &P, const WaveLds 
     const int L = P.L, M = sdf.M, nq = L * M;
     auto append = [&](bool cand, float d, int key) {
         const uint64_t mask = __ballot(cand);
-        if (cand) {
-            const int pos = ncand + mask_rank(mask);
-            lds.cand_d[pos] = d;
-            lds.cand_k[pos] = key;
-        }
+        if (cand) lds.cand[ncand + mask_rank(mask)] = pack_gap_key(d, key);
         ncand += __popcll(mask);
     };
     for (int i0 = 0; i0 < nq; i0 += WAVE) {
@@ -480,7 +446,7 @@ __device__ __forceinline__ void narrow_phase_sdf(const Consts &P, const WaveLds 
 template <typename SR, bool SDF = false>
 __device__ __forceinline__ void step_setup(const Consts &P, const float *__restrict__ seg,
                                            const float *__restrict__ sph, int S, const float *inv_in, const Body &B,
-                                           int wkey, const float *wr, const WaveLds &lds, StepStats &stats,
+                                           float reach, int wkey, const float *wr, const WaveLds &lds, StepStats &stats,
                                            StepState<SR> &st, const SdfRef &sdf = SdfRef())
 {
     const int lane = lane_here();
@@ -488,10 +454,8 @@ __device__ __forceinline__ void step_setup(const Consts &P, const float *__restr
     step_pose<SR>(P, inv_in, B, st);
     const float *R = st.R;
 
-    // 2. narrow phase: lanes over spheres, candidates appended to LDS in
-    //    (sphere block, link) order by ballot + prefix count.  The links'
-    //    segment records (first 8 floats) sit in registers, one link per
-    //    lane, and are broadcast link by link.
+    // 2. narrow phase: the links' segment records (first 8 floats) one per
+    //    lane to begin with
     float sgr[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (lane < L) {
         const float4 a = *reinterpret_cast<const float4 *>(seg + lane * SEG_STRIDE);
@@ -506,9 +470,9 @@ __device__ __forceinline__ void step_setup(const Consts &P, const float *__restr
     if (SDF)
         narrow_phase_sdf(P, lds, sdf, seg, sph, S, B.x, R, ncand);
     else if (S * (L + 1) <= cap)
-        narrow_phase<false>(P, lds, sgr, sph, S, B.x, R, cap, ncand, removed);
+        narrow_phase<false>(P, lds, sgr, sph, S, reach, B.x, R, cap, ncand, removed);
     else
-        narrow_phase<true>(P, lds, sgr, sph, S, B.x, R, cap, ncand, removed);
+        narrow_phase<true>(P, lds, sgr, sph, S, reach, B.x, R, cap, ncand, removed);
     wave_sync();
     ncand = __builtin_amdgcn_readfirstlane(ncand);   // wave-uniform: loops on it stay scalar
     const int C = ncand < P.C_max ? ncand : P.C_max;
@@ -516,19 +480,20 @@ __device__ __forceinline__ void step_setup(const Consts &P, const float *__restr
     st.ncand = ncand;
     st.span = lane_span(C);
 
-    // 3. cap: rank of every candidate in (d, key) order; the C_max lowest
-    //    land in sel[rank].  More than one wave of candidates are first cut
-    //    to the C_max lowest by a radix select over as many words per lane
-    //    as there are (its registers and compares grow with them); then
-    //    each lane holds one as a packed (d, key) word and counts the lower
-    //    words, broadcast lane by lane.
+    // 3. cap: the C_max lowest candidates in (d, key) order, slot r the r-th.
+    //    More than one wave of candidates are first cut to the C_max lowest
+    //    by a radix select over as many words per lane as there are (its
+    //    registers and compares grow with them); then one word per lane is
+    //    sorted across the wavefront (64 words: a third of the time of
+    //    counting the lower ones broadcast lane by lane).
     if (ncand > WAVE) {
         const int n = cap_cut_pieces(lds, ncand, P.C_max);
         if (n <= 2 * WAVE) cap_cut<2>(lds, n, P.C_max);
         else if (n <= 4 * WAVE) cap_cut<4>(lds, n, P.C_max);
         else cap_cut<8>(lds, n, P.C_max);
     }
-    cap_rank(lds, ncand > WAVE ? P.C_max : ncand, P.C_max);
+    const int nw = ncand > WAVE ? P.C_max : ncand;
+    const uint64_t word = wave_sort(lane < nw ? lds.cand[lane] : ~0ull, nw);
     // previous warm cache to LDS for the key lookup
     lds.wkey[lane] = wkey;
     lds.wr[3 * lane + 0] = wr[0];
@@ -542,21 +507,22 @@ __device__ __forceinline__ void step_setup(const Consts &P, const float *__restr
 
     // 4. contact setup, one contact per lane, and the warm start from the
     //    previous step's impulse of the same key
-    //    (keys of the previous cache are unique; eight compared per round)
-    contact_setup<SR, SDF>(P, seg, sph, B, lane < C ? lds.sel[lane] : -1, st, sdf);
+    //    (keys of the previous cache are unique; sixteen compared per round)
+    contact_setup<SR, SDF>(P, seg, sph, B, lane < C ? (int)(uint32_t)word : -1, st, sdf);
     if (st.act) {
         int hit = -1;
-        for (int j = 0; j < P.C_max; j += 8) {
-            const int4 a = *reinterpret_cast<const int4 *>(lds.wkey + j);
-            const int4 b = *reinterpret_cast<const int4 *>(lds.wkey + j + 4);
-            hit = a.x == st.key ? j : hit;
-            hit = a.y == st.key ? j + 1 : hit;
-            hit = a.z == st.key ? j + 2 : hit;
-            hit = a.w == st.key ? j + 3 : hit;
-            hit = b.x == st.key ? j + 4 : hit;
-            hit = b.y == st.key ? j + 5 : hit;
-            hit = b.z == st.key ? j + 6 : hit;
-            hit = b.w == st.key ? j + 7 : hit;
+        // (past C_max the lookup's words hold no key)
+        for (int j = 0; j < P.C_max; j += 16) {
+            int4 a[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const int4 *>(lds.wkey + j + 4 * i);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                hit = a[i].x == st.key ? j + 4 * i : hit;
+                hit = a[i].y == st.key ? j + 4 * i + 1 : hit;
+                hit = a[i].z == st.key ? j + 4 * i + 2 : hit;
+                hit = a[i].w == st.key ? j + 4 * i + 3 : hit;
+            }
         }
         if (hit >= 0) {
             st.r[0] = lds.wr[3 * hit]; st.r[1] = lds.wr[3 * hit + 1]; st.r[2] = lds.wr[3 * hit + 2];
@@ -837,19 +803,6 @@ __device__ __forceinline__ void step_finish(const Consts &P, const StepState<SR>
     wr[2] = st.act ? (float)r[2] : 0.f;
     out_link = st.act ? st.link : -1;
     out_imp[0] = (float)impS[0]; out_imp[1] = (float)impS[1]; out_imp[2] = (float)impS[2];
-}
-
-// one full step of one simulation
-template <typename SR>
-__device__ __forceinline__ void env_step(const Consts &P, const float *__restrict__ seg,
-                                         const float *__restrict__ sph, int S, const float *inv_in, Body &B,
-                                         int &wkey, float *wr, int &out_link, float *out_imp, const WaveLds &lds,
-                                         StepStats &stats)
-{
-    StepState<SR> st;
-    step_setup<SR>(P, seg, sph, S, inv_in, B, wkey, wr, lds, stats, st);
-    step_solve<SR>(P, st, B.mu, inv_in, reinterpret_cast<SR *>(lds.cand_d));
-    step_finish<SR>(P, st, inv_in, B, wkey, wr, out_link, out_imp);
 }
 
 }  // namespace pt
