@@ -152,6 +152,7 @@ struct pt_batch_s {
     // the PD-controlled hand (hand_mode 1)
     int hand_mode = 0;
     pt::PdConsts Q = {};
+    int joint_rows() const { return hand_mode == 1 ? P.D : 0; } // of the observation, after its force rows
     int32_t *d_pd = nullptr;     // the hand's structure table (pt::PdTab)
     int32_t *d_parent = nullptr; // [K] parents of a resampling, for the joint state's copies
     float *d_pd_obs = nullptr;   // [4L + D][K] a step's observation inside a window of per-step kernels
@@ -676,11 +677,7 @@ pt_status pt_observe(pt_batch b, float *obs, pt_stream s)
 {
     if (!b) return fail(PT_E_ARG, "batch is NULL");
     if (!obs) return fail(PT_E_ARG, "obs is NULL");
-    if (b->hand_mode == 1) {
-        HIP_TRY(launch_observe_pd(b->P, b->d_contacts, b->hstate, obs, (hipStream_t)s));
-        return PT_OK;
-    }
-    HIP_TRY(launch_observe(b->P, b->d_contacts, b->d_cslip, b->d_seg, obs, (hipStream_t)s));
+    HIP_TRY(launch_observe(b->P, b->d_contacts, b->d_cslip, b->d_seg, b->hstate, b->joint_rows(), obs, (hipStream_t)s));
     return PT_OK;
 }
 
@@ -689,17 +686,12 @@ pt_status pt_cost(pt_batch b, const float *obs, const float *obs_gt, float *cost
     if (!b) return fail(PT_E_ARG, "batch is NULL");
     if (!obs || !obs_gt || !cost_sum) return fail(PT_E_ARG, "obs/obs_gt/cost_sum is NULL");
     hipStream_t st = (hipStream_t)s;
-    if (b->hand_mode == 1) {
-        HIP_TRY(launch_cost_pd(b->P, b->Q, b->d_group_of, obs, obs_gt, cost_sum, st));
-        if (best) HIP_TRY(launch_argmin(b->P.G, b->d_group_start, cost_sum, best, st));
-        return PT_OK;
-    }
     // up to FUSED_ARGMIN_MAX simulations the cost kernel's last workgroup ranks
     // the groups itself; past that one workgroup's pass over the population
     // takes longer than a launch of the per-group argmin kernel
-    const bool fused = best && b->P.K <= pt::FUSED_ARGMIN_MAX;
-    HIP_TRY(launch_cost(b->P, b->d_group_of, b->d_group_start, obs, obs_gt, cost_sum, fused ? best : nullptr,
-                        b->d_queue + 2, st));
+    const bool fused = best && b->hand_mode == 0 && b->P.K <= pt::FUSED_ARGMIN_MAX;
+    HIP_TRY(launch_cost(b->P, b->d_group_of, b->d_group_start, obs, obs_gt, b->Q.w_q, b->joint_rows(), cost_sum,
+                        fused ? best : nullptr, b->d_queue + 2, st));
     if (best && !fused) HIP_TRY(launch_argmin(b->P.G, b->d_group_start, cost_sum, best, st));
     return PT_OK;
 }
@@ -766,8 +758,9 @@ static pt_status enqueue_window(pt_batch b, const float *u_win, const float *obs
                 float *obs = obs_out ? obs_out + (size_t)t * RK : b->d_pd_obs;
                 HIP_TRY(launch_step_pd(P, b->Q, tb, b->d_pd, u_win + (size_t)(t + 1) * P.D, state, params, warm,
                                        b->hstate, b->d_contacts, b->d_stats, st));
-                HIP_TRY(launch_observe_pd(P, b->d_contacts, b->hstate, obs, st));
-                HIP_TRY(launch_cost_pd(P, b->Q, b->d_group_of, obs, obs_gt_win + (size_t)t * RG, cost_sum, st));
+                HIP_TRY(launch_observe(P, b->d_contacts, nullptr, nullptr, b->hstate, P.D, obs, st));
+                HIP_TRY(launch_cost(P, b->d_group_of, b->d_group_start, obs, obs_gt_win + (size_t)t * RG, b->Q.w_q,
+                                    P.D, cost_sum, nullptr, nullptr, st));
             }
         }
         if (best) HIP_TRY(launch_argmin(P.G, b->d_group_start, cost_sum, best, st));

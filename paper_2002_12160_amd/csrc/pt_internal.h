@@ -114,10 +114,11 @@ hipError_t launch_step(const pt::Consts &P, const pt::Tables &tb, const float *u
                        float *params, float *warm, float *contacts, float *cslip, float *seg_out, int64_t *stats,
                        int waves_per_block, bool seg_in, hipStream_t s);
 size_t hand_fk_lds_bytes(int L, int D);
-hipError_t launch_observe(const pt::Consts &P, const float *contacts, const float *cslip, const float *seg, float *obs,
-                          hipStream_t s);
+hipError_t launch_observe(const pt::Consts &P, const float *contacts, const float *cslip, const float *seg,
+                          const float *hstate, int n_joint, float *obs, hipStream_t s);
 hipError_t launch_cost(const pt::Consts &P, const int32_t *group_of, const int32_t *group_start, const float *obs,
-                       const float *obs_gt, float *cost_sum, int32_t *best, int32_t *done, hipStream_t s);
+                       const float *obs_gt, float w_q, int n_joint, float *cost_sum, int32_t *best, int32_t *done,
+                       hipStream_t s);
 hipError_t launch_argmin(int G, const int32_t *group_start, const float *cost, int32_t *best, hipStream_t s);
 // the groups' simulations ranked by (cost, index), NaN as +inf: rank [K] (the
 // rank within its group), order [K] (by group, then rank: batch indices);
@@ -165,8 +166,4 @@ hipError_t launch_step_pd(const pt::Consts &P, const pt::PdConsts &Q, const pt::
 hipError_t launch_window_pd(const pt::Consts &P, const pt::PdConsts &Q, const pt::Tables &tb, const int32_t *pd_tab,
                             const float *u_win, float *state, float *params, float *warm, float *hstate,
                             const float *obs_gt_win, float *cost_sum, float *obs_out, int64_t *stats, hipStream_t s);
-hipError_t launch_observe_pd(const pt::Consts &P, const float *contacts, const float *hstate, float *obs,
-                             hipStream_t s);
-hipError_t launch_cost_pd(const pt::Consts &P, const pt::PdConsts &Q, const int32_t *group_of, const float *obs,
-                          const float *obs_gt, float *cost_sum, hipStream_t s);
 hipError_t launch_copy_hand(int K, int rows, const int32_t *parent, float *hstate, hipStream_t s);

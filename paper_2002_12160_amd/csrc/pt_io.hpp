@@ -124,7 +124,7 @@ __device__ __forceinline__ void flush_stats(int64_t *stats, const StepStats &st,
 // order are found by scalar bit scans, every lane reads them all (broadcast)
 // and add, under a branch, takes what is its own: one lane has it, and masked
 // sums cost a select beside every add (the Eq. 3 window of 4096 simulations:
-// 1566 us with selects and a walk each for force and slip, 1499 us as it is).
+// 1566 us with selects and a walk each for force and slip, 1455 us as it is).
 template <typename Read, typename Add>
 __device__ __forceinline__ void for_contacts(uint64_t on, Read read, Add add)
 {
@@ -220,45 +220,38 @@ __device__ __forceinline__ void slip_record(const StepState<SR> &st, const float
     out[4] = rn * sv[0]; out[5] = rn * sv[1]; out[6] = rn * sv[2]; out[7] = q;
 }
 
-// Eq. 3 observation of sensor `lane` (lanes < L) from the step's staged
-// contacts -- stage [C_max][4] (link, impulse), slip [C_max][8] -- and the
-// step's segment records: |c|, c/|c| as sensor_force; with n_bar the
-// normalised sum r_n n and s = sum r_n s / sum r_n, d = s in the sensor's
-// surface frame (e1 = the link axis projected normal to n_bar, or the
-// contact-frame rule if the normal runs along the axis; e2 = n_bar x e1),
-// normalised, when |s| > tau_slip, else 0; rot = the sign of
-// sum q / |sum r_n n| beyond tau_spin, else 0.  o[7].
-__device__ __forceinline__ bool sensor_obs_eq3(const Consts &P, const float *stage, const float *slip,
-                                               const float *seg, int link, float *o)
-{
-    const int lane = lane_here();
-    o[4] = o[5] = o[6] = 0.f;
+// One sensor's sums over a step's contacts: the impulse, and for Eq. 3
+// sum r_n n, sum r_n s, sum r_n and sum q of the slip records
+struct SensorSums {
     float f0 = 0.f, f1 = 0.f, f2 = 0.f, N[3] = {0.f, 0.f, 0.f}, S[3] = {0.f, 0.f, 0.f}, W = 0.f, Q = 0.f;
-    struct Rec {
-        float4 f, a, b;
-    };
-    for_contacts(
-        __ballot(link >= 0),
-        [&](int c) {
-            return Rec{*reinterpret_cast<const float4 *>(stage + 4 * c),
-                       *reinterpret_cast<const float4 *>(slip + SLIP_STRIDE * c),
-                       *reinterpret_cast<const float4 *>(slip + SLIP_STRIDE * c + 4)};
-        },
-        [&](const Rec &r) {
-            if (__float_as_int(r.f.x) == lane) {
-                f0 += r.f.y; f1 += r.f.z; f2 += r.f.w;
-                N[0] += r.a.x; N[1] += r.a.y; N[2] += r.a.z; W += r.a.w;
-                S[0] += r.b.x; S[1] += r.b.y; S[2] += r.b.z; Q += r.b.w;
-            }
-        });
-    force_obs(P, f0, f1, f2, o);
-    if (lane >= P.L) return false;
-    const float nn = sqrtf(dot3(N, N));
-    if (!(W > 0.f) || !(nn > 0.f)) return true;
-    const float nb[3] = {N[0] / nn, N[1] / nn, N[2] / nn};
-    const float sl[3] = {S[0] / W, S[1] / W, S[2] / W};
+    __device__ __forceinline__ void add_force(const float4 &f)
+    {
+        f0 += f.y; f1 += f.z; f2 += f.w;
+    }
+    __device__ __forceinline__ void add_slip(const float4 &a, const float4 &b)
+    {
+        N[0] += a.x; N[1] += a.y; N[2] += a.z; W += a.w;
+        S[0] += b.x; S[1] += b.y; S[2] += b.z; Q += b.w;
+    }
+};
+
+// Eq. 3 observation of sensor l from its sums and the step's segment records
+// seg: |c|, c/|c| as sensor_force; with n_bar the normalised sum r_n n and
+// s = sum r_n s / sum r_n, d = s in the sensor's surface frame (e1 = the link
+// axis projected normal to n_bar, or the contact-frame rule if the normal
+// runs along the axis; e2 = n_bar x e1), normalised, when |s| > tau_slip,
+// else 0; rot = the sign of sum q / |sum r_n n| beyond tau_spin, else 0.
+// o[7].
+__device__ __forceinline__ void eq3_obs(const Consts &P, const SensorSums &m, const float *seg, int l, float *o)
+{
+    force_obs(P, m.f0, m.f1, m.f2, o);
+    o[4] = o[5] = o[6] = 0.f;
+    const float nn = sqrtf(dot3(m.N, m.N));
+    if (!(m.W > 0.f) || !(nn > 0.f)) return;
+    const float nb[3] = {m.N[0] / nn, m.N[1] / nn, m.N[2] / nn};
+    const float sl[3] = {m.S[0] / m.W, m.S[1] / m.W, m.S[2] / m.W};
     if (sqrtf(dot3(sl, sl)) > P.tau_slip) {
-        const float *sg = seg + lane * SEG_STRIDE;
+        const float *sg = seg + l * SEG_STRIDE;
         const float la = sqrtf(sg[4] * sg[4] + sg[5] * sg[5] + sg[6] * sg[6]);
         const float ea[3] = {sg[4] / la, sg[5] / la, sg[6] / la};
         const float an = dot3(ea, nb);
@@ -274,8 +267,36 @@ __device__ __forceinline__ bool sensor_obs_eq3(const Consts &P, const float *sta
         const float dn = sqrtf(d1 * d1 + d2 * d2);
         if (dn > 0.f) { o[4] = d1 / dn; o[5] = d2 / dn; }
     }
-    const float spin = Q / nn;
+    const float spin = m.Q / nn;
     o[6] = spin > P.tau_spin ? 1.f : (spin < -P.tau_spin ? -1.f : 0.f);
+}
+
+// The Eq. 3 observation of sensor `lane` (lanes < L) from the step's staged
+// contacts -- stage [C_max][4] (link, impulse), slip [C_max][8].  Returns
+// false on lanes >= L.
+__device__ __forceinline__ bool sensor_obs_eq3(const Consts &P, const float *stage, const float *slip,
+                                               const float *seg, int link, float *o)
+{
+    const int lane = lane_here();
+    SensorSums m;
+    struct Rec {
+        float4 f, a, b;
+    };
+    for_contacts(
+        __ballot(link >= 0),
+        [&](int c) {
+            return Rec{*reinterpret_cast<const float4 *>(stage + 4 * c),
+                       *reinterpret_cast<const float4 *>(slip + SLIP_STRIDE * c),
+                       *reinterpret_cast<const float4 *>(slip + SLIP_STRIDE * c + 4)};
+        },
+        [&](const Rec &r) {
+            if (__float_as_int(r.f.x) == lane) {
+                m.add_force(r.f);
+                m.add_slip(r.a, r.b);
+            }
+        });
+    if (lane >= P.L) return false;
+    eq3_obs(P, m, seg, lane, o);
     return true;
 }
 
@@ -290,6 +311,10 @@ __device__ __forceinline__ float unit_angle(const float *a, const float *b, int 
     }
     return 2.f * atan2f(sqrtf(dm), sqrtf(dp));
 }
+
+// The joint-angle term of the step cost (Eq. 3's w_1 term), added to the
+// running sum cs: w_q d^2 with d = q - q_gt.
+__device__ __forceinline__ float pd_joint_cost(float cs, float w_q, float d) { return cs + w_q * d * d; }
 
 // Eq. 3 cost of one sensor: w4 (1 - alpha) + alpha (w5 |dM| + w6 angle of
 // the forces when in contact) + w7 (1 - beta) + beta w8 angle of the slip

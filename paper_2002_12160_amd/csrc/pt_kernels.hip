@@ -316,90 +316,135 @@ __global__ __launch_bounds__(StepBounds<SR>::threads) void k_step(Consts P, Tabl
     flush_stats(stats, st, 1, e);
 }
 
-// one wavefront per simulation, lanes over sensors
-// (cost_mode 1: the seven rows of Eq. 3's observation, from the contacts'
-// slip records and the step's segments)
-__global__ __launch_bounds__(256) void k_observe(Consts P, const float *__restrict__ contacts,
-                                                 const float *__restrict__ cslip, const float *__restrict__ seg,
-                                                 float *__restrict__ obs)
+// The observation of the last step: a workgroup stages the contacts of
+// OBS_SIMS simulations in LDS, a thread per (simulation, sensor) sums its own
+// in contact order.  cost_mode 1 (EQ3): the seven rows of Eq. 3, from the
+// contacts' slip records and the step's segments.  PD hand: J rows of joint
+// angles from hstate follow the force rows.  Bound by the walk over all
+// contact slots (a wavefront per simulation with its lanes over sensors did
+// three times the walks, and wrote 16 bytes at a time instead of 64):
+// 16384 simulations, 64 slots: 23.3 -> 8.7 us; 256 simulations of 32:
+// 4.7 -> 4.5 us.  A simulation's records are offset by 16 bytes from the
+// last one's, so that the lanes' reads at one slot fall in different banks.
+constexpr int OBS_SIMS = 16;
+template <bool EQ3>
+__global__ __launch_bounds__(1024) void k_observe(Consts P, const float *__restrict__ contacts,
+                                                  const float *__restrict__ cslip, const float *__restrict__ seg,
+                                                  const float *__restrict__ hstate, int J, float *__restrict__ obs)
 {
-    __shared__ __align__(16) float stage[4][WAVE * 4];
-    __shared__ __align__(16) float slip[4][WAVE * SLIP_STRIDE];
-    const int wib = threadIdx.x / WAVE;
-    const int e = xcd_block(blockIdx.x, gridDim.x) * (blockDim.x / WAVE) + wib;
-    if (e >= P.K) return;
-    const int lane = lane_id();
-    float *sg = stage[wib];
-    float *sl = slip[wib];
-    const bool eq3 = P.cost_mode == 1;
-    int link = -1;
-    if (lane < P.C_max) {
-        const float4 rec = *reinterpret_cast<const float4 *>(contacts + ((size_t)e * P.C_max + lane) * 4);
-        *reinterpret_cast<float4 *>(sg + 4 * lane) = rec;
-        link = __float_as_int(rec.x);
-        if (eq3) {
-            const float4 *src = reinterpret_cast<const float4 *>(cslip + ((size_t)e * P.C_max + lane) * SLIP_STRIDE);
-            *reinterpret_cast<float4 *>(sl + SLIP_STRIDE * lane) = src[0];
-            *reinterpret_cast<float4 *>(sl + SLIP_STRIDE * lane + 4) = src[1];
-        }
+    extern __shared__ __align__(16) float4 obs_lds[];
+    const int C = P.C_max, fs = C + 1, ss = 2 * C + 1;
+    float4 *force = obs_lds, *slip = obs_lds + OBS_SIMS * fs;
+    const int e0 = xcd_block(blockIdx.x, gridDim.x) * OBS_SIMS, n = min(OBS_SIMS, P.K - e0);
+    const float4 *src = reinterpret_cast<const float4 *>(contacts) + (size_t)e0 * C;
+    for (int i = threadIdx.x; i < n * C; i += blockDim.x) force[i + i / C] = src[i];
+    if constexpr (EQ3) {
+        const float4 *from = reinterpret_cast<const float4 *>(cslip) + (size_t)e0 * C * 2;
+        for (int i = threadIdx.x; i < n * C * 2; i += blockDim.x) slip[i + i / (2 * C)] = from[i];
     }
-    wave_sync();
-    const size_t LK = (size_t)P.L * P.K;
-    float o[7];
-    const bool sensor = eq3 ? sensor_obs_eq3(P, sg, sl, seg, link, o) : sensor_force(P, sg, link, o);
-    if (sensor) {
-        const int R = eq3 ? 7 : 4;
+    const size_t K = P.K, LK = P.L * K;
+    for (int i = threadIdx.x; i < J * OBS_SIMS; i += blockDim.x) {
+        const int s = i % OBS_SIMS, j = i / OBS_SIMS;
+        if (s < n) obs[4 * LK + j * K + e0 + s] = hstate[j * K + e0 + s];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < P.L * OBS_SIMS; i += blockDim.x) {
+        const int s = i % OBS_SIMS, l = i / OBS_SIMS;
+        if (s >= n) continue;
+        const float4 *f = force + s * fs, *w = slip + s * ss;
+        SensorSums m;
+#pragma unroll 8
+        for (int c = 0; c < C; ++c) {
+            const float4 r = f[c];
+            if (__float_as_int(r.x) == l) {
+                m.add_force(r);
+                if constexpr (EQ3) m.add_slip(w[2 * c], w[2 * c + 1]);
+            }
+        }
+        constexpr int R = EQ3 ? 7 : 4;
+        float o[R];
+        if constexpr (EQ3) eq3_obs(P, m, seg, l, o);
+        else force_obs(P, m.f0, m.f1, m.f2, o);
 #pragma unroll
-        for (int j = 0; j < 7; ++j)
-            if (j < R) obs[j * LK + (size_t)lane * P.K + e] = o[j];
+        for (int j = 0; j < R; ++j) obs[j * LK + l * K + e0 + s] = o[j];
     }
 }
 
-
-// one thread per simulation, its sensors' terms summed in sensor order (the
-// order of step_cost_wave, so the plain and batched paths add the same
-// bits); obs_gt is [R][L][G] (the observed batch's own observation layout)
-// (R = 4: force rows; R = 7: the rows of Eq. 3)
-constexpr int COST_THREADS = 256;
-template <int R>
-__global__ __launch_bounds__(COST_THREADS) void k_cost(Consts P, const int32_t *__restrict__ group_of,
-                                                       const int32_t *__restrict__ group_start,
-                                                       const float *__restrict__ obs,
-                                                       const float *__restrict__ obs_gt, float *cost_sum,
-                                                       int32_t *__restrict__ best, int32_t *done)
+// The step cost: a thread per (simulation, sensor) makes the terms, COST_ROWS
+// sensors of SIMS simulations at a time through LDS, a thread per simulation
+// sums them in sensor order (the order of step_cost_wave, so the plain and
+// batched paths add the same bits); obs_gt is [R][L][G] (the observed
+// batch's own observation layout; R = 4: force rows; R = 7: the rows of
+// Eq. 3).  PD hand: J joint rows follow, their w_q (q_j - q_gt_j)^2 in joint
+// order.  Latency-bound: a thread per simulation that walks its sensors has
+// few wavefronts and a chain of loads (16384 simulations: 9.3 -> 5.0 us; with
+// the PD hand's joints 14.3 -> 5.3 us; 256 simulations, with the ranking:
+// 7.5 -> 5.6 us).
+// SIMS: 256 where the launch also ranks (`best`), so that up to 256
+// simulations are one workgroup, which needs no counter, and the ranking has
+// 1024 threads; otherwise 16, which gives 16384 simulations four workgroups
+// a compute unit.
+constexpr int COST_ROWS = 32;
+template <int R, int SIMS>
+__global__ __launch_bounds__(1024) void k_cost(Consts P, const int32_t *__restrict__ group_of,
+                                               const int32_t *__restrict__ group_start,
+                                               const float *__restrict__ obs, const float *__restrict__ obs_gt,
+                                               float w_q, int J, float *cost_sum, int32_t *__restrict__ best,
+                                               int32_t *done)
 {
-    const int e = blockIdx.x * COST_THREADS + threadIdx.x;
-    __shared__ float csum[COST_THREADS];
-    if (e < P.K) {
-        const int g = P.G == 1 ? 0 : group_of[e];
-        const size_t LK = (size_t)P.L * P.K, LG = (size_t)P.L * P.G;
-        constexpr bool eq3 = R == 7;
-        const float prev = cost_sum[e];
-        float cs = 0.f;
-        // CH sensors' loads in flight at a time, then their terms in order
-        constexpr int CH = eq3 ? 8 : 16;
-        for (int l0 = 0; l0 < P.L; l0 += CH) {
+    __shared__ float term[COST_ROWS][SIMS];
+    __shared__ float csum[SIMS];
+    const int e0 = blockIdx.x * SIMS, nt = blockDim.x;
+    const size_t LK = (size_t)P.L * P.K, LG = (size_t)P.L * P.G;
+    // a thread's simulation is the same in every item: nt is a multiple of SIMS
+    const int s = threadIdx.x % SIMS, e = min(e0 + s, P.K - 1), r0 = threadIdx.x / SIMS, dr = nt / SIMS;
+    const int g = P.G == 1 ? 0 : group_of[e];
+    const bool sums = threadIdx.x < SIMS && e0 + s < P.K;
+    const float prev = sums ? cost_sum[e] : 0.f;
+    float cs = 0.f;
+    for (int l0 = 0; l0 < P.L; l0 += COST_ROWS) {
+        const int n = min(COST_ROWS, P.L - l0);
+        // CH sensors' loads in flight at a time
+        constexpr int CH = SIMS < 256 ? 1 : 4;
+        for (int r = r0; r < n; r += CH * dr) {
             float o[CH][R], gt[CH][R];
-            // the simulation's own rows first: they do not wait for g
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const size_t l = l0 + min(r + c * dr, n - 1);
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    o[c][j] = obs[j * LK + l * P.K + e];
+                    gt[c][j] = obs_gt[j * LG + l * P.G + g];
+                }
+            }
 #pragma unroll
             for (int c = 0; c < CH; ++c)
-#pragma unroll
-                for (int j = 0; j < R; ++j)
-                    o[c][j] = l0 + c < P.L ? obs[j * LK + (size_t)(l0 + c) * P.K + e] : 0.f;
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-#pragma unroll
-                for (int j = 0; j < R; ++j)
-                    gt[c][j] = l0 + c < P.L ? obs_gt[j * LG + (size_t)(l0 + c) * P.G + g] : 0.f;
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-                if (l0 + c < P.L) {
-                    if constexpr (eq3) cs += sensor_cost_eq3(P, o[c], gt[c]);
-                    else cs += sensor_cost(P, o[c], gt[c]);
+                if (r + c * dr < n) {
+                    if constexpr (R == 7) term[r + c * dr][s] = sensor_cost_eq3(P, o[c], gt[c]);
+                    else term[r + c * dr][s] = sensor_cost(P, o[c], gt[c]);
                 }
         }
+        __syncthreads();
+        if (sums) {
+#pragma unroll 8
+            for (int r = 0; r < n; ++r) cs += term[r][s];
+        }
+        __syncthreads();
+    }
+    for (int j0 = 0; j0 < J; j0 += COST_ROWS) {
+        const int n = min(COST_ROWS, J - j0);
+        for (int r = r0; r < n; r += dr)
+            term[r][s] = obs[R * LK + (size_t)(j0 + r) * P.K + e] - obs_gt[R * LG + (size_t)(j0 + r) * P.G + g];
+        __syncthreads();
+        if (sums) {
+#pragma unroll 8
+            for (int r = 0; r < n; ++r) cs = pd_joint_cost(cs, w_q, term[r][s]);
+        }
+        __syncthreads();
+    }
+    if (sums) {
         cost_sum[e] = prev + cs;
-        csum[threadIdx.x] = prev + cs;
+        csum[s] = prev + cs;
     }
     // with `best`: the workgroup that finishes last ranks every group (Eq. 2);
     // a single workgroup ranks its own sums from LDS, with no counter
@@ -742,24 +787,38 @@ hipError_t launch_step(const Consts &P, const Tables &tb, const float *u_prev, c
     return hipGetLastError();
 }
 
-hipError_t launch_observe(const Consts &P, const float *contacts, const float *cslip, const float *seg, float *obs,
-                          hipStream_t s)
+hipError_t launch_observe(const Consts &P, const float *contacts, const float *cslip, const float *seg,
+                          const float *hstate, int n_joint, float *obs, hipStream_t s)
 {
-    int blocks = (P.K + 3) / 4;
-    hipLaunchKernelGGL(k_observe, dim3(blocks), dim3(256), 0, s, P, contacts, cslip, seg, obs);
+    const bool eq3 = P.cost_mode == 1;
+    const int blocks = (P.K + OBS_SIMS - 1) / OBS_SIMS;
+    const int threads = std::min(1024, (P.L * OBS_SIMS + WAVE - 1) / WAVE * WAVE);
+    const size_t lds = sizeof(float4) * OBS_SIMS * (P.C_max + 1 + (eq3 ? 2 * P.C_max + 1 : 0));
+    if (eq3)
+        hipLaunchKernelGGL(k_observe<true>, dim3(blocks), dim3(threads), lds, s, P, contacts, cslip, seg, hstate,
+                           n_joint, obs);
+    else
+        hipLaunchKernelGGL(k_observe<false>, dim3(blocks), dim3(threads), lds, s, P, contacts, cslip, seg, hstate,
+                           n_joint, obs);
     return hipGetLastError();
 }
 
 hipError_t launch_cost(const Consts &P, const int32_t *group_of, const int32_t *group_start, const float *obs,
-                       const float *obs_gt, float *cost_sum, int32_t *best, int32_t *done, hipStream_t s)
+                       const float *obs_gt, float w_q, int n_joint, float *cost_sum, int32_t *best, int32_t *done,
+                       hipStream_t s)
 {
-    int blocks = (P.K + COST_THREADS - 1) / COST_THREADS;
+    // threads: a multiple of the simulations of a workgroup, a row of sensors
+    // or joints for each
+    auto go = [&](auto kernel, int sims) {
+        const int rows = std::max(1, std::min(COST_ROWS, std::max(P.L, n_joint)));
+        const int threads = std::min(1024, (rows * sims + WAVE - 1) / WAVE * WAVE);
+        hipLaunchKernelGGL(kernel, dim3((P.K + sims - 1) / sims), dim3(threads), 0, s, P, group_of, group_start, obs,
+                           obs_gt, w_q, n_joint, cost_sum, best, done);
+    };
     if (P.cost_mode == 1)
-        hipLaunchKernelGGL(k_cost<7>, dim3(blocks), dim3(COST_THREADS), 0, s, P, group_of, group_start, obs, obs_gt,
-                           cost_sum, best, done);
+        best ? go(k_cost<7, 256>, 256) : go(k_cost<7, 16>, 16);
     else
-        hipLaunchKernelGGL(k_cost<4>, dim3(blocks), dim3(COST_THREADS), 0, s, P, group_of, group_start, obs, obs_gt,
-                           cost_sum, best, done);
+        best ? go(k_cost<4, 256>, 256) : go(k_cost<4, 16>, 16);
     return hipGetLastError();
 }
 

@@ -10,9 +10,6 @@
 //   k_window_pd    the batched window: T steps per wavefront with the
 //                  observation and step cost of every step (the same bits
 //                  as the per-step kernels)
-//   k_observe_pd   per-sensor contact force of the last step and the
-//                  simulation's joint angles (the observation of Sec. III-A)
-//   k_cost_pd      step cost: the force terms plus w_q |q - q_gt|^2
 //   k_copy_hand    the resampler's copies of the joint state
 #include "pt_io.hpp"
 #include "pt_pd.hpp"
@@ -83,8 +80,8 @@ __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2))) void 
 // Batched window of the PD hand: one wavefront per simulation runs the T
 // steps of the window (commands u_win rows 1..T), each with the per-step
 // kernel's code, its observation (force rows, then the joint angles) and
-// the step cost of k_cost_pd added to the simulation's running sum: the
-// same bits as T rounds of k_step_pd, k_observe_pd and k_cost_pd.  State,
+// the step cost of k_cost added to the simulation's running sum: the
+// same bits as T rounds of k_step_pd, k_observe and k_cost.  State,
 // joint state and warm cache stay on chip between the steps.
 // obs_gt_win [T][4L + D][G]; obs_out [T][4L + D][K] or NULL.
 template <bool SDF, int G>
@@ -167,7 +164,7 @@ __global__ __launch_bounds__(WAVE) void k_window_pd(Consts P, PdConsts Q, Tables
         if (ob && lane < D) ob[4 * LK + (size_t)jl * K + e] = qv;
         // sensors in sensor order, then the joints in row order
         float cs = step_cost_wave(P, cl);
-        for (int j = 0; j < D; ++j) cs = pd_joint_cost(cs, Q.w_q, qrow[j], gt[4 * LG + (size_t)j * P.G + g]);
+        for (int j = 0; j < D; ++j) cs = pd_joint_cost(cs, Q.w_q, qrow[j] - gt[4 * LG + (size_t)j * P.G + g]);
         wave_sync();
         cost += cs;
     }
@@ -179,58 +176,6 @@ __global__ __launch_bounds__(WAVE) void k_window_pd(Consts P, PdConsts Q, Tables
     store_warm(warm, P.C_max, e, wkey, wr);
     if (lane == 0) cost_sum[e] = cost;
     flush_stats(stats, st, P.T, e);
-}
-
-// one wavefront per simulation, lanes over sensors, then over joints:
-// obs rows [4][L] of force terms followed by the D joint angles
-__global__ __launch_bounds__(256) void k_observe_pd(Consts P, const float *__restrict__ contacts,
-                                                    const float *__restrict__ hstate, float *__restrict__ obs)
-{
-    __shared__ __align__(16) float stage[4][WAVE * 4];
-    const int wib = threadIdx.x / WAVE;
-    const int e = xcd_block(blockIdx.x, gridDim.x) * (blockDim.x / WAVE) + wib;
-    if (e >= P.K) return;
-    const int lane = lane_id();
-    float *sg = stage[wib];
-    int link = -1;
-    if (lane < P.C_max) {
-        const float4 rec = *reinterpret_cast<const float4 *>(contacts + ((size_t)e * P.C_max + lane) * 4);
-        *reinterpret_cast<float4 *>(sg + 4 * lane) = rec;
-        link = __float_as_int(rec.x);
-    }
-    wave_sync();
-    const size_t LK = (size_t)P.L * P.K;
-    float o[7];
-    if (sensor_force(P, sg, link, o)) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) obs[j * LK + (size_t)lane * P.K + e] = o[j];
-    }
-    for (int j = lane; j < P.D; j += WAVE) obs[4 * LK + (size_t)j * P.K + e] = hstate[(size_t)j * P.K + e];
-}
-
-// one thread per simulation: the sensors' terms in sensor order (as k_cost),
-// then the joints' w_q (q_j - q_gt_j)^2 in joint order; obs_gt [4L + D][G]
-__global__ __launch_bounds__(256) void k_cost_pd(Consts P, PdConsts Q, const int32_t *__restrict__ group_of,
-                                                 const float *__restrict__ obs, const float *__restrict__ obs_gt,
-                                                 float *cost_sum)
-{
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= P.K) return;
-    const int g = P.G == 1 ? 0 : group_of[e];
-    const size_t LK = (size_t)P.L * P.K, LG = (size_t)P.L * P.G;
-    float cs = 0.f;
-    for (int l = 0; l < P.L; ++l) {
-        float o[4], gt[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            o[j] = obs[j * LK + (size_t)l * P.K + e];
-            gt[j] = obs_gt[j * LG + (size_t)l * P.G + g];
-        }
-        cs += sensor_cost(P, o, gt);
-    }
-    for (int j = 0; j < P.D; ++j)
-        cs = pd_joint_cost(cs, Q.w_q, obs[4 * LK + (size_t)j * P.K + e], obs_gt[4 * LG + (size_t)j * P.G + g]);
-    cost_sum[e] += cs;
 }
 
 // joint state rows of every resampled simulation from its parent (parents
@@ -298,21 +243,6 @@ hipError_t launch_window_pd(const Consts &P, const PdConsts &Q, const Tables &tb
         small ? go(k_window_pd<true, 4>) : go(k_window_pd<true, PD_GMAX>);
     else
         small ? go(k_window_pd<false, 4>) : go(k_window_pd<false, PD_GMAX>);
-    return hipGetLastError();
-}
-
-hipError_t launch_observe_pd(const Consts &P, const float *contacts, const float *hstate, float *obs,
-                             hipStream_t s)
-{
-    const int blocks = (P.K + 3) / 4;
-    hipLaunchKernelGGL(k_observe_pd, dim3(blocks), dim3(4 * WAVE), 0, s, P, contacts, hstate, obs);
-    return hipGetLastError();
-}
-
-hipError_t launch_cost_pd(const Consts &P, const PdConsts &Q, const int32_t *group_of, const float *obs,
-                          const float *obs_gt, float *cost_sum, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_cost_pd, dim3((P.K + 255) / 256), dim3(256), 0, s, P, Q, group_of, obs, obs_gt, cost_sum);
     return hipGetLastError();
 }
 

@@ -906,12 +906,4 @@ __device__ __forceinline__ void pd_step(const Consts &P, const PdConsts &Q, cons
     step_finish<double>(P, sst, inv, B, wkey, wr, link, imp);
 }
 
-// The joint-angle term of the step cost (Eq. 3's w_1 term), added to the
-// running sum cs: w_q (q - q_gt)^2.
-__device__ __forceinline__ float pd_joint_cost(float cs, float w_q, float q, float q_gt)
-{
-    const float d = q - q_gt;
-    return cs + w_q * d * d;
-}
-
 }  // namespace pt
