@@ -17,7 +17,8 @@
 //   k_refine_gather   the elites' window starts; the scaled gradient step is
 //                     the reverse sweep's last act and keep-or-halve the
 //                     forward sweep's (kernels of their own waited behind the
-//                     sweeps that fill the GPU: 130 us a gradient step)
+//                     sweeps that fill the GPU, 130 us a gradient step in
+//                     parts that overlap: the real-time window 9.81 -> 9.72 ms)
 #include <algorithm>
 
 #include "pt_adjoint.hpp"

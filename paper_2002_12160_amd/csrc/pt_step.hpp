@@ -204,7 +204,7 @@ __device__ __forceinline__ void contact_setup(const Consts &P, const float *__re
 // to 512 candidates, where every lane used to rank its words against the
 // list in LDS, that is ~500 instead of ~5000 instructions (three control
 // steps of a fresh 16384-simulation population, ~265 candidates each: 2.25 ms
-// with the LDS ranking, 1.56 ms with the cut).
+// with the LDS ranking, 1.56 ms with the cut, all else as it was then).
 template <int H>
 __device__ __forceinline__ uint64_t cap_cut(const WaveLds &lds, int n, int C_max)
 {
@@ -322,7 +322,10 @@ __device__ __forceinline__ int compact_candidates(const WaveLds &lds, int n, int
 // 128 spheres has within the margin by the squared distance (1e-4 of slack,
 // a thousand times its rounding): no square root, no append.  Two thirds of
 // the real-time population's narrow phase were links read lane by lane, a
-// square root for every pair and one block's appends waiting for the other's.
+// square root for every pair and one block's appends waiting for the other's
+// (three control steps of 16384 simulations, with the kept words' order and
+// the sensors' reads reworked too: 1545 -> 1477 us).  What is left is the
+// latency of read, square root, ballot and append for each link in reach.
 // Bounded: the list may fill up; when it may not hold another link's and the
 // table's candidates (4 x 64 entries; with no link in reach the table alone
 // cannot fill it) it is cut to its C_max lowest, and from then on only
