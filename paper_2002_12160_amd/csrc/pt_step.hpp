@@ -567,6 +567,19 @@ __device__ __forceinline__ void step_solve(const Consts &P, StepState<SR> &st, f
         // first iteration they are those of the line search's accepted trial
         SR u[3];
         rel_velocity(st, nu, r, eps, u);
+        // An empty slot adds its Jacobian times its zero frame to the sums: 0,
+        // if the Jacobian is finite.  At r = u = 0 it is not where fb_delta^4
+        // underflows (float32, fb_delta below 1e-11), so there the empty slots
+        // stand on contact 0's r and u: finite whenever that contact is, and
+        // six selects a step instead of one for each sum and iteration.
+        if constexpr (sizeof(SR) == 4) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const SR r0 = bcast_lane(r[i], 0), u0 = bcast_lane(u[i], 0);
+                r[i] = act ? r[i] : r0;
+                u[i] = act ? u[i] : u0;
+            }
+        }
         FBOut<SR> fo;
         fb_value(mu, kap, del, r, u, fo);
         const SR mass = body_mass_entry(Mb);
@@ -740,6 +753,10 @@ __device__ __forceinline__ void step_solve(const Consts &P, StepState<SR> &st, f
             if (sizeof(SR) == 8) psi = st.psi_end;
 #pragma unroll
             for (int i = 0; i < 6; ++i) nu[i] += alpha * dn[i];
+        }
+        if constexpr (sizeof(SR) == 4) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) r[i] = act ? r[i] : SR(0);
         }
     }
     // fresh sum of the body velocity for the final impulses
