@@ -441,12 +441,13 @@ __device__ __forceinline__ void stage_costs(const float *__restrict__ cost, int 
 
 // True in every thread of the workgroup that arrives last among the grid's
 // workgroups, counted on *done (0 before the launch); that workgroup sees the
-// global writes every other one made before its call.  The caller's last
-// workgroup puts *done back to 0 for the next launch.  Every thread of every
-// workgroup calls it once.  flag: one int of LDS, free for the call.
-__device__ __forceinline__ bool last_block(int32_t *done, int *flag)
+// global writes that every other one's threads with `wrote` made before the
+// call.  The caller's last workgroup puts *done back to 0 for the next launch.
+// Every thread of every workgroup calls it once.  flag: one int of LDS, free
+// for the call.
+__device__ __forceinline__ bool last_block(int32_t *done, int *flag, bool wrote = true)
 {
-    __threadfence();
+    if (wrote) __threadfence();
     __syncthreads();
     if (threadIdx.x == 0) *flag = atomicAdd(done, 1) == (int)gridDim.x - 1;
     __syncthreads();
@@ -456,20 +457,36 @@ __device__ __forceinline__ bool last_block(int32_t *done, int *flag)
 }
 
 // Per-group argmin of cost over [group_start[g], group_start[g + 1]) by one
-// workgroup (at most 1024 threads): the lowest index of the minimum with NaN
-// ranked as +inf, the group's start for an empty group.  (cost, index) pairs
-// are totally ordered, so the result does not depend on the order in which
-// the threads combine.  sv, si: 16 entries each of LDS, free for the call.
+// workgroup (at most 1024 threads, whole wavefronts): the lowest index of the
+// minimum with NaN ranked as +inf, the group's start for an empty group.
+// (cost, index) pairs are totally ordered, so the result does not depend on
+// the order in which the threads combine.  The wavefronts divide among the
+// groups, side by side and with at most one barrier in all; one group after
+// another by the whole workgroup takes two barriers and a walk over the
+// wavefronts' results for each, which grow with the wavefronts (k_cost with 16
+// groups of 256 simulations: 31 us by 4 wavefronts, 48 us by 16, side by side
+// 10.4 us; 3 groups of 683: 12.4, 17.8 and 9.7 us).
+// sv, si: 16 entries each of LDS, free for the call.
 __device__ __forceinline__ void block_argmin(int G, const int32_t *__restrict__ group_start, const float *cost,
                                              int32_t *__restrict__ best, float *sv, int *si)
 {
-    const int lane = lane_id(), w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
-    const int nt = blockDim.x;
-    for (int g = 0; g < G; ++g) {
-        const int lo = group_start[g], hi = group_start[g + 1];
-        float bv = __int_as_float(0x7f800000);
-        int bi = 0x7fffffff;
-        for (int i0 = lo + threadIdx.x; i0 < hi; i0 += 4 * nt) {
+    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), nw = blockDim.x / WAVE;
+    const int tw = max(1, nw / G);                       // wavefronts per group
+    const int team = w / tw, member = w - team * tw;
+    float bv;
+    int bi;
+    auto lowest = [&](int lanes) {
+        for (int off = lanes / 2; off > 0; off >>= 1) {
+            const float x = __shfl_xor(bv, off);
+            const int i = __shfl_xor(bi, off);
+            if (x < bv || (x == bv && i < bi)) { bv = x; bi = i; }
+        }
+    };
+    for (int g = team; g < G; g += nw / tw) {            // once where tw > 1
+        const int lo = group_start[g], hi = group_start[g + 1], nt = tw * WAVE;
+        bv = __int_as_float(0x7f800000);
+        bi = 0x7fffffff;
+        for (int i0 = lo + member * WAVE + lane; i0 < hi; i0 += 4 * nt) {
             float v[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) v[k] = i0 + k * nt < hi ? cost[i0 + k * nt] : 0.f;
@@ -480,20 +497,19 @@ __device__ __forceinline__ void block_argmin(int G, const int32_t *__restrict__ 
                 if (i < hi && (x < bv || (x == bv && i < bi))) { bv = x; bi = i; }
             }
         }
-#pragma unroll
-        for (int off = WAVE / 2; off > 0; off >>= 1) {
-            const float x = __shfl_xor(bv, off);
-            const int i = __shfl_xor(bi, off);
-            if (x < bv || (x == bv && i < bi)) { bv = x; bi = i; }
+        lowest(WAVE);
+        if (lane == 0) {
+            if (tw == 1) best[g] = bi == 0x7fffffff ? lo : bi;
+            else { sv[w] = bv; si[w] = bi; }
         }
-        if (lane == 0) { sv[w] = bv; si[w] = bi; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            for (int k = 1; k < nw; ++k)
-                if (sv[k] < bv || (sv[k] == bv && si[k] < bi)) { bv = sv[k]; bi = si[k]; }
-            best[g] = bi == 0x7fffffff ? lo : bi;
-        }
-        __syncthreads();
+    }
+    if (tw == 1) return;
+    __syncthreads();
+    if (team < G && member == 0) {
+        bv = lane < tw ? sv[w + lane] : __int_as_float(0x7f800000);
+        bi = lane < tw ? si[w + lane] : 0x7fffffff;
+        lowest(16);
+        if (lane == 0) best[team] = bi == 0x7fffffff ? group_start[team] : bi;
     }
 }
 

@@ -381,9 +381,12 @@ __global__ __launch_bounds__(1024) void k_observe(Consts P, const float *__restr
 // the PD hand's joints 14.3 -> 5.3 us; 256 simulations, with the ranking:
 // 7.5 -> 5.6 us).
 // SIMS: 256 where the launch also ranks (`best`), so that up to 256
-// simulations are one workgroup, which needs no counter, and the ranking has
-// 1024 threads; otherwise 16, which gives 16384 simulations four workgroups
-// a compute unit.
+// simulations are one workgroup, which needs no counter (4.8 us of 256; 257
+// and its counter 8.6 us), and beyond that few workgroups take part in the
+// counting: only the wavefronts that wrote sums flush them first (one group of
+// 512: 12.4 us when all 16 did, 9.1 us; a thread per simulation in 256-thread
+// workgroups 8.9 us, of 4096 11.3 against 10.0 us).  Otherwise 16, which gives
+// 16384 simulations four workgroups a compute unit.
 constexpr int COST_ROWS = 32;
 template <int R, int SIMS>
 __global__ __launch_bounds__(1024) void k_cost(Consts P, const int32_t *__restrict__ group_of,
@@ -454,7 +457,7 @@ __global__ __launch_bounds__(1024) void k_cost(Consts P, const int32_t *__restri
     if (gridDim.x == 1) {
         __syncthreads();
         block_argmin(P.G, group_start, csum, best, sv, si);
-    } else if (last_block(done, si + 16)) {
+    } else if (last_block(done, si + 16, sums)) {
         block_argmin(P.G, group_start, cost_sum, best, sv, si);
         if (threadIdx.x == 0) *done = 0;
     }
