@@ -72,9 +72,12 @@ __host__ __device__ inline int elite_count(int n, float elite_frac)
 // running sums fit in one workgroup's LDS)
 constexpr int MAX_GROUP = 16384;
 
-// The resampler ranks and copies a group of up to RESAMPLE_ONE simulations in
-// one workgroup; larger groups are ranked RANK_CHUNK simulations per
-// workgroup and copied COPY_CHUNK per workgroup, over the whole GPU
+// Where a batch's largest group has up to RESAMPLE_ONE simulations, the
+// resampler ranks and copies each group in one workgroup; otherwise all its
+// groups are ranked RANK_CHUNK simulations per workgroup and copied COPY_CHUNK
+// per workgroup, over the whole GPU (device time: 64 groups of 256 11.7 us in
+// one workgroup each, 14.5 in pieces; 63 of 16 and one of 257 11.2 in pieces,
+// 26 sorted in a workgroup each)
 constexpr int RESAMPLE_ONE = 256;
 constexpr int RANK_CHUNK = WAVE;
 constexpr int COPY_CHUNK = 16;

@@ -519,8 +519,16 @@ __global__ __launch_bounds__(1024) void k_rank(float elite_frac, const int2 *__r
 // ranking alone) are cleared.  Bound by the copies' latency and, for large
 // populations, their bytes: 16 groups of 1024 with 64-slot warm caches (13 MB
 // copied) take 53 us in one workgroup per group, 8 + 10 us like this; one
-// group of 16384 777 and 46; a group of 256 is 3 us faster in one workgroup
-// (one launch) than in two kernels.
+// group of 16384 777 and 46; a group of 256 is 1 to 3 us faster in one
+// workgroup (one launch) than in two kernels.
+// A workgroup per group, sized for the largest, has four threads per
+// simulation and four wavefronts at least: a group's latency.  Past
+// RESAMPLE_MANY groups these no longer run side by side, so groups of up to 16
+// get one wavefront (4096 groups of 4: 15.4 us with four, 12.4 with one; 1024
+// groups of 4: 6.8 and 8.6), and where the largest is more than four times the
+// mean they are cut into pieces (3000 groups of 4 and one of 256: 32.7 us with
+// 1024 threads for each, 19.1 in pieces; 1000 of 4 and one of 100: 11.2, 11.8).
+constexpr int RESAMPLE_MANY = 1536;
 template <bool ONE>
 __global__ __launch_bounds__(1024) void k_resample(Consts P, ResampleArgs R, const int2 *__restrict__ piece,
                                                    const int32_t *__restrict__ group_start, uint32_t window_idx,
@@ -539,6 +547,13 @@ __global__ __launch_bounds__(1024) void k_resample(Consts P, ResampleArgs R, con
     const int m = min(n - i0, M);   // simulations of this workgroup
     const int kb = elite_count(n, R.elite_frac);
     const size_t K = P.K;
+    if (kb >= n) {   // all elites: nothing is copied
+        for (int s = tid; s < m; s += nt) {
+            if (parent) parent[lo + i0 + s] = -1;
+            cost_sum[lo + i0 + s] = 0.f;
+        }
+        return;
+    }
     if constexpr (ONE) {
         stage_costs(cost_sum + lo, n, cs);
         __syncthreads();
@@ -589,12 +604,16 @@ __global__ __launch_bounds__(1024) void k_resample(Consts P, ResampleArgs R, con
     float4 *w4 = reinterpret_cast<float4 *>(warm);
     const int C = P.C_max;
     const int items = m * C;
+    // x / C and x / m by the reciprocal: x below 2^14 and the divisor at most
+    // 256, so (x + 1/2) / d is farther from an integer than its rounding
+    const float per_slot = 1.f / (float)C, per_row = 1.f / (float)m;
+    auto sim = [&](int x) { return (int)(((float)x + 0.5f) * per_slot); };
     auto source = [&](int x) {
-        const int s = min(x, items - 1) / C, p = par[s];
-        return w4[(size_t)(p < 0 ? lo + i0 + s : p) * C + (min(x, items - 1) - s * C)];
+        const int y = min(x, items - 1), s = sim(y), p = par[s];
+        return w4[(size_t)(p < 0 ? lo + i0 + s : p) * C + (y - s * C)];
     };
     auto copy = [&](int x, const float4 &v) {
-        if (x < items && par[x / C] >= 0) w4[(size_t)(lo + i0) * C + x] = v;
+        if (x < items && par[sim(x)] >= 0) w4[(size_t)(lo + i0) * C + x] = v;
     };
     for (int x = tid; x < items; x += 4 * nc) {
         const float4 a = source(x), b = source(x + nc), c = source(x + 2 * nc), d = source(x + 3 * nc);
@@ -605,7 +624,7 @@ __global__ __launch_bounds__(1024) void k_resample(Consts P, ResampleArgs R, con
     }
     // state rows, a row's simulations in order
     for (int x = tid; x < 13 * m; x += nc) {
-        const int c = x / m, s = x - c * m, p = par[s];
+        const int c = (int)(((float)x + 0.5f) * per_row), s = x - c * m, p = par[s];
         if (p >= 0) state[(size_t)c * K + lo + i0 + s] = state[(size_t)c * K + p];
     }
 }
@@ -846,8 +865,10 @@ hipError_t launch_resample(const Consts &P, const ResampleArgs &R, const int32_t
                            int32_t *rank, int32_t *order, float *state, float *params, float *warm, int32_t *parent,
                            hipStream_t s)
 {
-    if (max_group <= RESAMPLE_ONE) {
-        const int threads = std::max(256, std::min(1024, (4 * max_group + WAVE - 1) / WAVE * WAVE));
+    const bool many = P.G > RESAMPLE_MANY, mixed = max_group > 64 && (size_t)max_group * P.G > 4 * (size_t)P.K;
+    if (max_group <= RESAMPLE_ONE && !(many && mixed)) {
+        const int per = many && max_group <= 16 ? 1 : 4;
+        const int threads = std::max(WAVE * per, std::min(1024, (per * max_group + WAVE - 1) / WAVE * WAVE));
         hipLaunchKernelGGL(k_resample<true>, dim3(P.G), dim3(threads), 0, s, P, R, nullptr, group_start, window_idx,
                            cost_sum, nullptr, nullptr, state, params, warm, parent);
         return hipGetLastError();
