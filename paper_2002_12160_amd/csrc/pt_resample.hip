@@ -20,12 +20,14 @@ namespace pt {
 
 // threads of a group's workgroup: REPS's uniform arithmetic (logarithms and
 // divisions, as much as an evaluation's work on four simulations) is done by
-// every wavefront, so small groups take few of them (16 groups of 1024: 256
-// threads 26 us, 1024 threads 37 us); past DRAW_SMALL the draws'
-// searches, a chain of LDS reads each, want as many as there are
+// every wavefront, so its groups take few of them up to 2048 (one group of
+// 2048, the call: 256 threads 38.4 us, 1024 threads 44.0); WRS has none of it
+// and only the draws' searches, a chain of LDS reads each, which want as many
+// as there are from four per thread on (one group of 1024: 256 threads 15.9
+// us, 1024 threads 16.3; of 1200 18.4 and 17.6, of 2048 22.6 and 18.9)
 constexpr int DRAW_THREADS = 1024;
 constexpr int DRAW_THREADS_SMALL = 256;
-constexpr int DRAW_SMALL = 2048;
+constexpr int draw_small(int kind) { return kind == 1 ? 2048 : 1024; }
 constexpr int DRAW_WAVES = DRAW_THREADS / WAVE;   // at most
 // REPS's temperature: Newton steps until one is below REPS_TOL in log(eta),
 // then a bisection of the bracket (width 60) for a function that will not
@@ -174,7 +176,8 @@ __global__ __launch_bounds__(NT) void k_weighted_draw(int kind, float hyper, con
             // In t = log(eta) its derivative is -Var / eta^2, Var the variance
             // of c under P, and log KL is a line of slope -2 where eta is
             // large: Newton on log(KL / eps) from the bracket's upper end
-            // takes 5 to 8 evaluations where bisection takes 48, a step
+            // takes 5 to 10 evaluations at eps = 1 and log-normal costs (29
+            // at 1e-8) where bisection takes 48, a step
             // that leaves the bracket is replaced by its middle.  Each
             // evaluation is one exp per simulation, two levels of DPP sums
             // and a barrier, ~2 us; 16 groups of 1024: 140 us with the
@@ -347,8 +350,8 @@ hipError_t launch_weighted_resample(const Consts &P, const ResampleArgs &R, int 
         hipLaunchKernelGGL(kern, dim3(P.G), dim3(threads), weighted_draw_lds_bytes(max_group), s, kind, hyper,
                            group_start, cost_sum, n_steps, window_idx, R.seed, weights, eta, parent);
     };
-    max_group <= DRAW_SMALL ? draw(k_weighted_draw<DRAW_THREADS_SMALL>, DRAW_THREADS_SMALL)
-                            : draw(k_weighted_draw<DRAW_THREADS>, DRAW_THREADS);
+    max_group <= draw_small(kind) ? draw(k_weighted_draw<DRAW_THREADS_SMALL>, DRAW_THREADS_SMALL)
+                                  : draw(k_weighted_draw<DRAW_THREADS>, DRAW_THREADS);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t total = (size_t)18 * P.K + (size_t)P.K * P.C_max;
