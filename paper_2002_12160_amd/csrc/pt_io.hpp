@@ -301,7 +301,10 @@ __device__ __forceinline__ bool sensor_obs_eq3(const Consts &P, const float *sta
 }
 
 // angle between two unit vectors of n components, 2 atan2(|a - b|, |a + b|)
-// (no loss of accuracy near 0 or pi)
+// (no loss of accuracy near 0 or pi).  The empty asm holds the arctangent in
+// its caller's branch: where it was hoisted out of one, its division lost the
+// precision it is declared with and was formed by another sequence, and one
+// kernel's costs were an ulp or two off the others'.
 __device__ __forceinline__ float unit_angle(const float *a, const float *b, int n)
 {
     float dm = 0.f, dp = 0.f;
@@ -309,6 +312,7 @@ __device__ __forceinline__ float unit_angle(const float *a, const float *b, int 
         dm += (a[i] - b[i]) * (a[i] - b[i]);
         dp += (a[i] + b[i]) * (a[i] + b[i]);
     }
+    asm volatile("" : "+v"(dm), "+v"(dp));
     return 2.f * atan2f(sqrtf(dm), sqrtf(dp));
 }
 
