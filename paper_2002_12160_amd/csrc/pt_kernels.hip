@@ -316,26 +316,29 @@ __global__ __launch_bounds__(StepBounds<SR>::threads) void k_step(Consts P, Tabl
     flush_stats(stats, st, 1, e);
 }
 
-// The observation of the last step: a workgroup stages the contacts of
-// OBS_SIMS simulations in LDS, a thread per (simulation, sensor) sums its own
-// in contact order.  cost_mode 1 (EQ3): the seven rows of Eq. 3, from the
+// The observation of the last step: a workgroup stages the contacts of SIMS
+// simulations in LDS, a thread per (simulation, sensor) sums its own in
+// contact order.  cost_mode 1 (EQ3): the seven rows of Eq. 3, from the
 // contacts' slip records and the step's segments.  PD hand: J rows of joint
 // angles from hstate follow the force rows.  Bound by the walk over all
-// contact slots (a wavefront per simulation with its lanes over sensors did
-// three times the walks, and wrote 16 bytes at a time instead of 64):
-// 16384 simulations, 64 slots: 23.3 -> 8.7 us; 256 simulations of 32:
-// 4.7 -> 4.5 us.  A simulation's records are offset by 16 bytes from the
-// last one's, so that the lanes' reads at one slot fall in different banks.
-constexpr int OBS_SIMS = 16;
-template <bool EQ3>
+// contact slots; a simulation's records are offset by 16 bytes from the last
+// one's, so that the lanes' reads at one slot fall in different banks.
+// SIMS: 16 where that still gives every compute unit a workgroup, past
+// OBS_FEW simulations, as their rows are written 64 bytes at a time (64 slots,
+// 20 sensors; a wavefront per simulation with its lanes over sensors, 4 and 16
+// simulations: 8192 of them 7.9, 6.1 and 5.0 us, 16384 12.8 us and, with 16,
+// 6.8); up to there 4, whose slots are staged in one go (9 sensors, 256
+// simulations: 4.4, 3.4 and 4.9 us).
+constexpr int OBS_FEW = 4096;
+template <bool EQ3, int SIMS>
 __global__ __launch_bounds__(1024) void k_observe(Consts P, const float *__restrict__ contacts,
                                                   const float *__restrict__ cslip, const float *__restrict__ seg,
                                                   const float *__restrict__ hstate, int J, float *__restrict__ obs)
 {
     extern __shared__ __align__(16) float4 obs_lds[];
     const int C = P.C_max, fs = C + 1, ss = 2 * C + 1;
-    float4 *force = obs_lds, *slip = obs_lds + OBS_SIMS * fs;
-    const int e0 = xcd_block(blockIdx.x, gridDim.x) * OBS_SIMS, n = min(OBS_SIMS, P.K - e0);
+    float4 *force = obs_lds, *slip = obs_lds + SIMS * fs;
+    const int e0 = xcd_block(blockIdx.x, gridDim.x) * SIMS, n = min(SIMS, P.K - e0);
     const float4 *src = reinterpret_cast<const float4 *>(contacts) + (size_t)e0 * C;
     for (int i = threadIdx.x; i < n * C; i += blockDim.x) force[i + i / C] = src[i];
     if constexpr (EQ3) {
@@ -343,13 +346,13 @@ __global__ __launch_bounds__(1024) void k_observe(Consts P, const float *__restr
         for (int i = threadIdx.x; i < n * C * 2; i += blockDim.x) slip[i + i / (2 * C)] = from[i];
     }
     const size_t K = P.K, LK = P.L * K;
-    for (int i = threadIdx.x; i < J * OBS_SIMS; i += blockDim.x) {
-        const int s = i % OBS_SIMS, j = i / OBS_SIMS;
+    for (int i = threadIdx.x; i < J * SIMS; i += blockDim.x) {
+        const int s = i % SIMS, j = i / SIMS;
         if (s < n) obs[4 * LK + j * K + e0 + s] = hstate[j * K + e0 + s];
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < P.L * OBS_SIMS; i += blockDim.x) {
-        const int s = i % OBS_SIMS, l = i / OBS_SIMS;
+    for (int i = threadIdx.x; i < P.L * SIMS; i += blockDim.x) {
+        const int s = i % SIMS, l = i / SIMS;
         if (s >= n) continue;
         const float4 *f = force + s * fs, *w = slip + s * ss;
         SensorSums m;
@@ -812,16 +815,17 @@ hipError_t launch_step(const Consts &P, const Tables &tb, const float *u_prev, c
 hipError_t launch_observe(const Consts &P, const float *contacts, const float *cslip, const float *seg,
                           const float *hstate, int n_joint, float *obs, hipStream_t s)
 {
-    const bool eq3 = P.cost_mode == 1;
-    const int blocks = (P.K + OBS_SIMS - 1) / OBS_SIMS;
-    const int threads = std::min(1024, (P.L * OBS_SIMS + WAVE - 1) / WAVE * WAVE);
-    const size_t lds = sizeof(float4) * OBS_SIMS * (P.C_max + 1 + (eq3 ? 2 * P.C_max + 1 : 0));
-    if (eq3)
-        hipLaunchKernelGGL(k_observe<true>, dim3(blocks), dim3(threads), lds, s, P, contacts, cslip, seg, hstate,
+    auto go = [&](auto kernel, int sims) {
+        const int threads = std::max(256, std::min(1024, (P.L * sims + WAVE - 1) / WAVE * WAVE));
+        const size_t lds = sizeof(float4) * sims * (P.C_max + 1 + (P.cost_mode == 1 ? 2 * P.C_max + 1 : 0));
+        hipLaunchKernelGGL(kernel, dim3((P.K + sims - 1) / sims), dim3(threads), lds, s, P, contacts, cslip, seg, hstate,
                            n_joint, obs);
+    };
+    const bool few = P.K <= OBS_FEW;
+    if (P.cost_mode == 1)
+        few ? go(k_observe<true, 4>, 4) : go(k_observe<true, 16>, 16);
     else
-        hipLaunchKernelGGL(k_observe<false>, dim3(blocks), dim3(threads), lds, s, P, contacts, cslip, seg, hstate,
-                           n_joint, obs);
+        few ? go(k_observe<false, 4>, 4) : go(k_observe<false, 16>, 16);
     return hipGetLastError();
 }
 
