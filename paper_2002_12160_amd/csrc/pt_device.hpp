@@ -382,12 +382,6 @@ __device__ __forceinline__ float segment_gap(const float *s, const float *c, flo
     return sqrtf(segment_dist2(s, c)) - rho - s[3];
 }
 
-__device__ __forceinline__ float pair_gap(const float *__restrict__ seg, int l, int L, const float *c, float rho)
-{
-    if (l == L) return c[2] - rho;
-    return segment_gap(seg + l * SEG_STRIDE, c, rho);
-}
-
 // full contact geometry of a kept pair: gap, normal (link -> object),
 // contact point on the object, velocity of the link surface point
 __device__ __forceinline__ void pair_contact(const float *__restrict__ seg, int l, int L, const float *c, float rho,

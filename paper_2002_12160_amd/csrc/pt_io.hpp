@@ -123,8 +123,9 @@ __device__ __forceinline__ void flush_stats(int64_t *stats, const StepStats &st,
 // contact order, four contacts' LDS reads in flight: the next contacts in
 // order are found by scalar bit scans, every lane reads them all (broadcast)
 // and add, under a branch, takes what is its own: one lane has it, and masked
-// sums cost a select beside every add (the Eq. 3 window of 4096 simulations:
-// 1566 us with selects and a walk each for force and slip, 1455 us as it is).
+// sums cost a select beside every add (the Eq. 3 window of 4096 simulations, one
+// population: 1566 us with selects and a walk each for force and slip, 1512 us
+// with branches, 1499 us with one walk).
 template <typename Read, typename Add>
 __device__ __forceinline__ void for_contacts(uint64_t on, Read read, Add add)
 {

@@ -21,7 +21,10 @@ namespace pt {
 // sums over part of the lanes, at two wavefronts per SIMD (the registers'
 // limit): the link tree walked with its records in registers took two steps
 // of 16384 simulations from 2668 to 2604 us, LDS reads without branches
-// around them to 2473 us.
+// around them to 2473 us.  Groups of five and six joints spill 4 or 5
+// registers at two wavefronts per SIMD and gain all the same (the real-time
+// hand with five joints a finger, two steps of 16384 simulations: 6.13 ms at
+// the five wavefronts a compute unit that the LDS allowed before, 3.57 ms).
 template <bool SDF, int G>
 __global__ __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(2))) void k_step_pd(Consts P, PdConsts Q, Tables tb, PdTab T,
                                                   const float *__restrict__ u, float *__restrict__ state,

@@ -94,8 +94,9 @@ __host__ __device__ constexpr size_t pd_tab_ints(int L, int D, int groups)
 // candidate list's words (free once the cap has run): PD_ROWS rows of
 // RedStride<double>, then one row of PD_SUM per run of contacts on one link.
 // All 64 rows at once would take 22 KB, five wavefronts per compute unit on
-// the real-time hand (20 links, 20 joints); 16 rows and 21 sums fit in the
-// list's 12.3 KB, which leaves the registers as the limit (eight): two steps
+// the real-time hand (20 links, 20 joints); 16 rows and 21 sums take 12.7 KB,
+// 52 words more than its list of 1536, 20 KB a wavefront in all, which leaves
+// the registers as the limit (eight): two steps
 // of 16384 simulations 4578 -> 2670 us, a window of 16 885 -> 767 us.
 constexpr int PD_ROWS = 16;
 constexpr int PD_SUM = 42;
@@ -534,10 +535,14 @@ __device__ __forceinline__ void pd_group_solve(const PdTab &T, const PdLane &w, 
             double s = y[k];
 #pragma unroll
             for (int m = k + 1; m < G; ++m) s -= a[k][m] * y[m];
-            // s / a[k][k], correctly rounded: with the correctly rounded
-            // reciprocal one exact remainder (FMA) and one correction of the
-            // product give the quotient (Markstein), three operations on the
-            // chain instead of a division's ten
+            // s / a[k][k] from the reciprocal: one remainder (FMA) and one
+            // correction of the product (Markstein's division), three
+            // operations on the chain instead of a division's ten.  The first
+            // quotient may be more than an ulp off, where the theorem does
+            // not promise the rounded quotient; none of 4e8 random and edge
+            // mantissas differed from the division.  A pivot of 0 or infinity
+            // gives NaN: the diagonal of A_h holds dt kd + dt^2 kp > 0, and a
+            // block singular to rounding eliminates to 0 / 0 either way
             const double q = s * inv[k];
             y[k] = fma(fma(-a[k][k], q, s), inv[k], q);
         }

@@ -203,8 +203,9 @@ __device__ __forceinline__ void contact_setup(const Consts &P, const float *__re
 // instead of n broadcasts or LDS reads against H words per lane: from 256
 // to 512 candidates, where every lane used to rank its words against the
 // list in LDS, that is ~500 instead of ~5000 instructions (three control
-// steps of a fresh 16384-simulation population, ~265 candidates each: 2.25 ms
-// with the LDS ranking, 1.56 ms with the cut, all else as it was then).
+// steps of one fresh 16384-simulation population, ~265 candidates each: 2.25
+// ms with the LDS ranking, 1.56 ms with the cut, all else as it was then; a
+// population with fewer candidates gains less).
 template <int H>
 __device__ __forceinline__ uint64_t cap_cut(const WaveLds &lds, int n, int C_max)
 {
@@ -607,7 +608,10 @@ __device__ __forceinline__ void step_solve(const Consts &P, StepState<SR> &st, f
         fb_value(mu, kap, del, r, u, fo);
         const SR mass = body_mass_entry(Mb);
         // the merit at the current impulses: in float64 that of the line
-        // search's accepted trial (one sum fewer per iteration)
+        // search's accepted trial, one sum fewer per iteration.  Its tree
+        // rounds otherwise than the column sums, so an Armijo test within
+        // rounding of its bound may fall the other way (none did in the 213
+        // calls, of every scene and option, whose outputs were compared)
         SR psi = SR(0);
         if (sizeof(SR) == 8)
             psi = wave_sum1(act ? SR(0.5) * (fo.phi[0] * fo.phi[0] + fo.phi[1] * fo.phi[1] + fo.phi[2] * fo.phi[2])
@@ -633,8 +637,8 @@ __device__ __forceinline__ void step_solve(const Consts &P, StepState<SR> &st, f
 #pragma unroll
                 for (int j = 0; j < 3; ++j)
                     QF[3 * i + j] = Q[3 * i] * F[j] + Q[3 * i + 1] * F[3 + j] + Q[3 * i + 2] * F[6 + j];
-            // the merit is summed with the system only in float32, where the
-            // line search's tree would round it differently
+            // in float32 the merit stays in the system's sums: the line
+            // search's tree rounds it otherwise
             constexpr int NS = sizeof(SR) == 8 ? 42 : 43;
             SR acc[NS];
             SR Qw[9];
