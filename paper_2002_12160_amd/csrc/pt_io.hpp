@@ -467,13 +467,13 @@ __device__ __forceinline__ bool last_block(int32_t *done, int *flag, bool wrote 
 // (cost, index) pairs are totally ordered, so the result does not depend on
 // the order in which the threads combine.  The wavefronts divide among the
 // groups, side by side and with at most one barrier in all; one group after
-// another by the whole workgroup takes two barriers and a walk over the
-// wavefronts' results for each, which grow with the wavefronts (k_cost with 16
-// groups of 256 simulations: 31 us by 4 wavefronts, 48 us by 16, side by side
-// 10.4 us; 3 groups of 683: 12.4, 17.8 and 9.7 us).
+// another by the whole workgroup (block_argmin) takes two barriers and a walk
+// over the wavefronts' results for each, which grow with the wavefronts
+// (k_cost with 16 groups of 256 simulations: 31 us by 4 wavefronts, 48 us by
+// 16, side by side 10.4 us; 3 groups of 683: 12.4, 17.8 and 9.7 us).
 // sv, si: 16 entries each of LDS, free for the call.
-__device__ __forceinline__ void block_argmin(int G, const int32_t *__restrict__ group_start, const float *cost,
-                                             int32_t *__restrict__ best, float *sv, int *si)
+__device__ __forceinline__ void team_argmin(int G, const int32_t *__restrict__ group_start, const float *cost,
+                                            int32_t *__restrict__ best, float *sv, int *si)
 {
     const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), nw = blockDim.x / WAVE;
     const int tw = max(1, nw / G);                       // wavefronts per group
@@ -515,6 +515,47 @@ __device__ __forceinline__ void block_argmin(int G, const int32_t *__restrict__ 
         bi = lane < tw ? si[w + lane] : 0x7fffffff;
         lowest(16);
         if (lane == 0) best[team] = bi == 0x7fffffff ? group_start[team] : bi;
+    }
+}
+
+// The same, group by group: the window kernel's, at most eight wavefronts.
+// With the teams its registers are allocated otherwise and the steps take
+// longer (16384 simulations of the real-time workload, 10 steps, no ranking in
+// the launch: 4.62 -> 4.69 ms).
+__device__ __forceinline__ void block_argmin(int G, const int32_t *__restrict__ group_start, const float *cost,
+                                             int32_t *__restrict__ best, float *sv, int *si)
+{
+    const int lane = lane_id(), w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
+    const int nt = blockDim.x;
+    for (int g = 0; g < G; ++g) {
+        const int lo = group_start[g], hi = group_start[g + 1];
+        float bv = __int_as_float(0x7f800000);
+        int bi = 0x7fffffff;
+        for (int i0 = lo + threadIdx.x; i0 < hi; i0 += 4 * nt) {
+            float v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = i0 + k * nt < hi ? cost[i0 + k * nt] : 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = i0 + k * nt;
+                const float x = v[k] != v[k] ? __int_as_float(0x7f800000) : v[k];
+                if (i < hi && (x < bv || (x == bv && i < bi))) { bv = x; bi = i; }
+            }
+        }
+#pragma unroll
+        for (int off = WAVE / 2; off > 0; off >>= 1) {
+            const float x = __shfl_xor(bv, off);
+            const int i = __shfl_xor(bi, off);
+            if (x < bv || (x == bv && i < bi)) { bv = x; bi = i; }
+        }
+        if (lane == 0) { sv[w] = bv; si[w] = bi; }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int k = 1; k < nw; ++k)
+                if (sv[k] < bv || (sv[k] == bv && si[k] < bi)) { bv = sv[k]; bi = si[k]; }
+            best[g] = bi == 0x7fffffff ? lo : bi;
+        }
+        __syncthreads();
     }
 }
 

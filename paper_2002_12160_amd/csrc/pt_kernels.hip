@@ -459,9 +459,9 @@ __global__ __launch_bounds__(1024) void k_cost(Consts P, const int32_t *__restri
     if (!best) return;
     if (gridDim.x == 1) {
         __syncthreads();
-        block_argmin(P.G, group_start, csum, best, sv, si);
+        team_argmin(P.G, group_start, csum, best, sv, si);
     } else if (last_block(done, si + 16, sums)) {
-        block_argmin(P.G, group_start, cost_sum, best, sv, si);
+        team_argmin(P.G, group_start, cost_sum, best, sv, si);
         if (threadIdx.x == 0) *done = 0;
     }
 }
@@ -472,7 +472,7 @@ __global__ void k_argmin(const int32_t *__restrict__ group_start, const float *_
 {
     __shared__ float sv[16];
     __shared__ int si[16];
-    block_argmin(1, group_start + blockIdx.x, cost, best + blockIdx.x, sv, si);
+    team_argmin(1, group_start + blockIdx.x, cost, best + blockIdx.x, sv, si);
 }
 
 // ---------------------------------------------------------------------
