@@ -82,9 +82,9 @@ MEASURED = {
     # traffic: (FETCH_SIZE x 1.9998 + WRITE_SIZE x 1.0000) KiB x 1024 per launch, the
     # factors from a 256 MiB device copy under the same counters; valu_*:
     # SQ_INSTS_VALU and SQ_ACTIVE_INST_VALU per launch, summed over the chip
-    "k_window_realtime16384": {"src": "68989093ea185dc4", "traffic": 397421582,
-                               "fetch": 28138395, "write": 369283187,
-                               "valu_insts": 2062095641, "valu_busy_quads": 2190110449},
+    "k_window_realtime16384": {"src": "b6fd48f5c92480d3", "traffic": 397904603,
+                               "fetch": 28500062, "write": 369404541,
+                               "valu_insts": 2062077209, "valu_busy_quads": 2190092017},
 }
 SIMDS, CLOCK_HZ = 1024, 2.4e9     # MI355X: 256 CUs x 4 SIMDs at 2.4 GHz; a VALU instruction issues in 4 cycles
 PEAK_F64_TFLOPS = 78.6            # MI355X published float64 vector peak (= non-packed float32)
